@@ -96,7 +96,9 @@ typedef struct muon_matrix_desc {
   int32_t tile_hint;                 /* 0: the planner's cost model picks the GEMM tile; 64, 128 or
                                         256: use that output tile for this matrix (a measured
                                         choice, e.g. from an autotuner's cache; Sec. 3.3 tunes the
-                                        schedule per shape).  256 needs 16-bit operands: with fp32
+                                        schedule per shape).  Either way it is the tile of launches
+                                        that fill the chip: a launch with fewer tiles may run on
+                                        smaller ones, with the same results.  256 needs 16-bit operands: with fp32
                                         NS (MUON_NS_FP32, or small m under bf16) it is UNSUPPORTED.
                                         Anything else is INVALID_ARG. */
 } muon_matrix_desc;
@@ -142,7 +144,9 @@ typedef struct muon_plan_info {
   int32_t n_buckets;                 /* distinct (m, n, padded shape, kernel class) */
   int32_t device;                    /* HIP device the plan lives on, -1 if host-only */
   int64_t workspace_bytes;           /* bytes muon_step needs */
-  int64_t launches_per_step;         /* kernel launches of one muon_step at max_ns_steps */
+  int64_t launches_per_step;         /* kernel launches of one muon_step at max_ns_steps, with one
+                                        of edge strips for every B*X of a 256-tile group that has
+                                        them (a B*X that runs on small tiles needs none) */
   double ns_flops_per_ns_step;       /* algorithmic flops of one NS step of Eq. 2 over all
                                         matrices: sum of 3 m^2 n + m^3 (symmetry-aware) */
   double padded_flops_per_ns_step;   /* flops those steps issue on padded tiles */

@@ -23,8 +23,8 @@ ARCH = "gfx950"
 # tile's B*X and square-output kernels per operand type, the smaller tiles)
 # so that they compile in parallel
 SOURCES = ["api.cpp", "plan.cpp", "ew_kernels.hip", "ns_gemm.hip", "ns_gemm_t256_bf16_bx.hip",
-           "ns_gemm_t256_bf16_sq.hip", "ns_gemm_t256_f16_bx.hip", "ns_gemm_t256_f16_sq.hip", "ns_gemm_small.hip",
-           "static_ws.hip"]
+           "ns_gemm_t256_bf16_sq.hip", "ns_gemm_t256_f16_bx.hip", "ns_gemm_t256_f16_sq.hip", "ns_tile_bf16.hip",
+           "ns_tile_f16.hip", "ns_tile_f32.hip", "static_ws.hip"]
 DIAG_SOURCES = ["diag/mfma_ceiling.hip"]
 DIAG_LIB_PATH = os.path.join(PKG, "libmuon_diag.so")
 

@@ -12,9 +12,9 @@
 namespace muon {
 
 // ---------------------------------------------------------------------------
-// Kernel classes: one GEMM configuration each.  Every class computes square
-// output tiles of TILE x TILE with 256 threads (2 x 2 waves) and a 128-byte
-// K slab per stage (64 bf16 or 32 fp32 values).
+// Kernel classes: one operand type and tile each, which set a matrix's padding
+// and its tile lists.  Every kernel computes square output tiles and moves K
+// in slabs of 128 bytes per row (64 16-bit or 32 fp32 values).
 // ---------------------------------------------------------------------------
 enum KernelClass : int32_t {
   KC_BF16_256 = 0,
@@ -111,6 +111,17 @@ struct MatHost {
   int64_t ws_bytes;    // workspace bytes of this matrix within its wave
 };
 
+// Kernels that can run a launch's tiles: the 256 tile, and the small tiles of
+// ns_tile_kernel.h with the number of K slabs in their LDS ring.
+enum Exec : int32_t { EX_256 = 0, EX_128_RING2 = 1, EX_128_RING3 = 2, EX_64_RING3 = 3, EX_COUNT = 4 };
+
+// How one kind of launch of a group runs: the kernel and its tile list.
+struct StageRun {
+  int32_t exec;
+  int64_t off;   // TileEntry offset
+  int32_t n;
+};
+
 // The matrices of one kernel class and one iteration form (Eq. 2 or the
 // Gram-space recurrence) within a wave, and their tile lists.
 struct ClassLaunch {
@@ -129,6 +140,9 @@ struct ClassLaunch {
   int32_t strip_kclass;
   int64_t strip_full_off;
   int32_t n_strip_full;
+  // the lists above are the class's own tiles; a launch with too few of them
+  // to fill the chip runs on smaller tiles instead (exec_tile in plan.cpp)
+  StageRun run_gram, run_square, run_full;
 };
 
 struct WaveHost {

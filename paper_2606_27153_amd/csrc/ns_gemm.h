@@ -1,8 +1,8 @@
 // Grouped Newton-Schulz GEMM launches: the arguments every launch takes,
 // and one launcher per group of kernel instantiations.  The kernels are in
-// ns_gemm_kernel.h; each group is instantiated in a translation unit of its
-// own (ns_gemm_t256_{bf16,f16}_{bx,sq}.hip, ns_gemm_small.hip), so that the
-// build compiles the groups in parallel.
+// ns_gemm_kernel.h and ns_tile_kernel.h; each group is instantiated in a translation unit of its
+// own (ns_gemm_t256_{bf16,f16}_{bx,sq}.hip, ns_tile_{bf16,f16,f32}.hip), so
+// that the build compiles the groups in parallel.
 #ifndef MUON_NS_GEMM_H
 #define MUON_NS_GEMM_H
 
@@ -42,8 +42,10 @@ int launch_t256_bf16_bx(bool padded, unsigned grid, const GemmArgs& g, hipStream
 int launch_t256_bf16_sq(bool padded, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
 int launch_t256_f16_bx(bool padded, unsigned grid, const GemmArgs& g, hipStream_t st);
 int launch_t256_f16_sq(bool padded, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
-// the 128 and 64 tile classes (16-bit and fp32), every stage
-int launch_small(int32_t kc, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
+// the small-tile kernels `exec` (Exec) of one operand type, every stage
+int launch_tile_bf16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
+int launch_tile_f16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
+int launch_tile_f32(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
 
 }  // namespace muon
 

@@ -11,24 +11,26 @@
 namespace muon {
 namespace {
 
-// One grouped launch of class kc over `nblocks` tiles (twice that for a
-// paired ST_SYM step, whose second half computes the second product).
-int launch_tiles(int32_t kc, bool padded, int32_t stage, const TileEntry* tiles, unsigned nblocks, bool pair,
-                 GemmArgs g, hipStream_t st) {
-  if (nblocks == 0) return 0;
-  g.tiles = tiles;
-  g.split = pair ? int32_t(nblocks) : INT32_MAX;
-  const unsigned grid = stage == ST_SYM && pair ? 2 * nblocks : nblocks;
-  switch (kc) {
+// One grouped launch over the tiles of `run` (twice that for a paired ST_SYM
+// step, whose second half computes the second product), on the kernels of
+// class kc's operand type.
+int launch_tiles(const Plan& p, int32_t kc, bool padded, int32_t stage, const StageRun& run, bool pair, GemmArgs g,
+                 hipStream_t st) {
+  if (run.n == 0) return 0;
+  g.tiles = p.d_tiles + run.off;
+  g.split = pair ? run.n : INT32_MAX;
+  const unsigned grid = unsigned(run.n) * (stage == ST_SYM && pair ? 2u : 1u);
+  const ClassInfo& ci = class_info(kc);
+  if (run.exec == EX_256) {
     // the 256 tile puts two waves on each SIMD, so a skipped wave speeds up
-    // its partner (the PAD instantiation); with one wave per SIMD (the
-    // 4-wave classes) nothing would
-    case KC_BF16_256:
-      return stage == ST_BX ? launch_t256_bf16_bx(padded, grid, g, st) : launch_t256_bf16_sq(padded, stage, grid, g, st);
-    case KC_F16_256:
+    // its partner (the PAD instantiation)
+    if (ci.f16)
       return stage == ST_BX ? launch_t256_f16_bx(padded, grid, g, st) : launch_t256_f16_sq(padded, stage, grid, g, st);
-    default: return launch_small(kc, stage, grid, g, st);
+    return stage == ST_BX ? launch_t256_bf16_bx(padded, grid, g, st) : launch_t256_bf16_sq(padded, stage, grid, g, st);
   }
+  return ci.fp32  ? launch_tile_f32(run.exec, stage, grid, g, st)
+         : ci.f16 ? launch_tile_f16(run.exec, stage, grid, g, st)
+                  : launch_tile_bf16(run.exec, stage, grid, g, st);
 }
 
 }  // namespace
@@ -57,15 +59,14 @@ int launch_ns_gemm(const Plan& p, const WaveHost& w, const ClassLaunch& cl, int3
   g.lr = sc.lr;
   g.decay = sc.decay;
   hipStream_t st = hipStream_t(stream);
-  const bool full = stage == ST_BX;
-  // the 256-tile part (the square outputs' row edge strips as half tiles
-  // among them), then for B*X the edge strips of the same matrices on the
-  // strip class's 128 tiles (their outputs are disjoint)
-  int e = launch_tiles(cl.kclass, cl.padded, stage, p.d_tiles + (full ? cl.full_off : cl.lower_off),
-                       unsigned(full ? cl.n_full : cl.n_lower), gs.pair != 0, g, st);
-  if (e == 0 && full && cl.strip_kclass >= 0)
-    e = launch_tiles(cl.strip_kclass, false, stage, p.d_tiles + cl.strip_full_off, unsigned(cl.n_strip_full),
-                     gs.pair != 0, g, st);
+  // a 256-tile B*X is followed by the edge strips of the same matrices on
+  // 128 tiles (their outputs are disjoint); any other launch covers its
+  // matrices' whole padded outputs
+  const StageRun& run = stage == ST_GRAM ? cl.run_gram : stage == ST_BX ? cl.run_full : cl.run_square;
+  int e = launch_tiles(p, cl.kclass, cl.padded, stage, run, gs.pair != 0, g, st);
+  if (e == 0 && stage == ST_BX && run.exec == EX_256)
+    e = launch_tiles(p, cl.kclass, false, stage, StageRun{EX_128_RING2, cl.strip_full_off, cl.n_strip_full}, false, g,
+                     st);
   return e;
 }
 

@@ -29,13 +29,16 @@
 // the tile with zeros, and the zeros stay zero through all products, so the
 // kernels need no bounds checks.
 //
-// Block: WGM x WGN waves (2 x 4 for the 256 tile, 2 x 2 otherwise), output
-// tile TILE x TILE, each wave owning a (TILE/WGM) x (TILE/WGN) piece made of
-// 32 x 32 MFMA blocks.  K advances in 128-byte slabs (64 bf16 or fp16 / 32
-// fp32) moved straight from global memory into double-buffered, XOR-swizzled
-// LDS by global_load_lds_dwordx4 (no staging registers).  Operands are bf16,
-// fp16 (the NS precision of the paper's implementation) or fp32; the 16-bit
-// kinds share every path and differ only in the MFMA instruction and the
+// This file holds the 256 x 256 tile kernel, which runs every launch that
+// fills the chip, and the building blocks it shares with the 128 and 64 tile
+// kernels of ns_tile_kernel.h.  Block: WGM x WGN waves (2 x 4 for the 256 tile,
+// 2 x 2 otherwise), output tile TILE x TILE, each wave owning a (TILE/WGM) x
+// (TILE/WGN) piece made of 32 x 32 MFMA blocks.  K advances in 128-byte slabs
+// (64 bf16 or fp16 / 32 fp32) moved straight from global memory into double-
+// buffered, XOR-swizzled LDS by global_load_lds_dwordx4 (no staging registers).
+// Operands are bf16, fp16 (the NS precision of the paper's implementation) or,
+// on the small tiles, fp32; the 16-bit kinds share every path and differ only
+// in the MFMA instruction and the conversions.
 #ifndef MUON_NS_GEMM_KERNEL_H
 #define MUON_NS_GEMM_KERNEL_H
 
@@ -559,6 +562,27 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
   }
 }
 
+// The update of one wave tile of the last B*X, for the matrix's orientation
+// and parameter type.
+template <class C>
+__device__ __forceinline__ void apply_update_tile(const f32x16 (&acc)[C::NBM][C::NBN], char* region,
+                                                  const GemmArgs& args, const MatDev& d, int64_t row0, int64_t col0,
+                                                  int lane) {
+  const PtrEntry pe = args.ptrs[d.index];
+  const float lrs = update_lr(args.lr, d.rows, d.cols);
+  if (d.param_dtype == MUON_BF16) {
+    if (d.transposed)
+      apply_via_lds<C, true, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+    else
+      apply_via_lds<C, false, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+  } else {
+    if (d.transposed)
+      apply_via_lds<C, true, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+    else
+      apply_via_lds<C, false, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // bf16 B*X reads its second operand straight from row-major X.  The slab of
 // X (64 K-rows x TILE columns) sits in LDS row-major; ds_read_b64_tr_b16
@@ -731,11 +755,13 @@ __device__ __forceinline__ void fuse_input(const char* sb, int kt, int row0, int
 // share of each slab and meets every barrier.  The other wave on its SIMD
 // then has the matrix core to itself.  Launches without padding use the
 // PAD = false instantiation, whose loop has no such tests.
-template <typename E, int TILE, int WGM, int WGN, int STAGE, bool PAD = false>
-__global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) {
-  using C = Cfg<E, TILE, WGM, WGN>;
-  // bf16 B*X takes its second operand from row-major X via transposing reads
-  constexpr bool TRB = STAGE == ST_BX && sizeof(E) == 2;
+template <typename E, int STAGE, bool PAD>
+__global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
+  constexpr int TILE = 256, WGN = 4;
+  using C = Cfg<E, TILE, 2, WGN>;
+  static_assert(sizeof(E) == 2, "16-bit operands");
+  // B*X takes its second operand from row-major X via transposing reads
+  constexpr bool TRB = STAGE == ST_BX;
   // Two LDS stages as distinct objects, so that the loads in flight into one
   // stage are known not to alias the reads of the other.
   __shared__ __attribute__((aligned(1024))) char stage0[2 * C::OPB];
@@ -765,10 +791,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
   // the K loop, with the blocks masked; each computed block is stored
   // transposed in its mirror position, and a block below the diagonal also as
   // computed, so the stored tile is symmetric like every off-diagonal pair.
-  // (A matrix one tile wide is left whole: in its short, latency-bound
-  // launches the second store pass costs more than the skipped blocks save.)
-  constexpr bool DSPLIT = TILE == 256 && WGM == 2 && WGN == 4 && sizeof(E) == 2 && STAGE != ST_BX;
-  const bool dtile = DSPLIT && ti == tj && args.mats[te.mat].m_pad > TILE;
+  const bool dtile = STAGE != ST_BX && ti == tj;
   // A half tile (kTileHalf: the row strip of a matrix whose padded m ends 128
   // rows into this tile) has only its top 128 rows, and its own operand
   // panel (on the diagonal of a square output, the other one too) only 128
@@ -780,8 +803,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
   // half tile (one per strip row) keeps the 128 x 64 pieces and computes, in
   // the masked K loop, the blocks of its real 128 x 128 part on or below the
   // diagonal, stored like a diagonal tile's.
-  constexpr bool HSPLIT = TILE == 256 && WGM == 2 && WGN == 4 && sizeof(E) == 2;
-  const bool htile = HSPLIT && STAGE != ST_BX && (te.flags & kTileHalf) != 0;
+  const bool htile = STAGE != ST_BX && (te.flags & kTileHalf) != 0;
   const bool hfast = htile && !dtile;
   int wm = wid / WGN, wn = wid % WGN;
   int wrow = wm * C::WTM;  // first row of the wave's piece within the tile
@@ -849,12 +871,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
     const E* b = reinterpret_cast<const E*>(args.ws + d.sq_off[bl]);
     K = mp;
     opa = b + int64_t(ti) * TILE * K;
-    if (TRB) {
-      // columns tj*TILE.. of row-major X (m_pad x n_pad)
-      opb = reinterpret_cast<const E*>(args.ws + d.x_off[args.pin]) + int64_t(tj) * TILE;
-    } else {
-      opb = reinterpret_cast<const E*>(args.ws + d.xt_off[args.pin]) + int64_t(tj) * TILE * K;
-    }
+    // columns tj*TILE.. of row-major X (m_pad x n_pad)
+    opb = reinterpret_cast<const E*>(args.ws + d.x_off[args.pin]) + int64_t(tj) * TILE;
   }
 
   f32x16 acc[C::NBM][C::NBN];
@@ -919,21 +937,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
         load_slab<C>(srcb, K, kt, st + C::OPB, wid);
     };
     typename Frag<E>::T fa0[CC::NBM], fb0[CC::NBN], fa1[CC::NBM], fb1[CC::NBN];
-    // fp32 operands: each slab's products are summed into a zeroed partial
-    // accumulator, which is added to the result after the slab.  This
-    // two-level sum keeps the rounding error of long K loops (K = n up to
-    // 14336 for the Gram product) near sqrt(K / 32) + sqrt(32) roundings
-    // instead of sqrt(K / 2), the chain of one accumulator through every
-    // 32x32x2 step.  The 16-bit classes accumulate directly.
-    f32x16 part[CC::NBM][CC::NBN];
-    if constexpr (sizeof(E) == 4) {
-#pragma unroll
-      for (int i = 0; i < CC::NBM; ++i)
-#pragma unroll
-        for (int j = 0; j < CC::NBN; ++j)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) part[i][j][q] = 0.f;
-    }
     auto first_frags = [&](const char* st) {
       if constexpr (TB)
         read_frags_tr<CC, E>(st, st + C::OPB, oa[0], ot, 0, fa0, fb0);
@@ -943,17 +946,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
     auto body = [&](const char* st, int kt) {
       if constexpr (TB) {
         slab_body_tr<CC, E>(st, oa, ot, fa0, fb0, fa1, fb1, a);
-      } else if constexpr (sizeof(E) == 4) {
-        slab_body<CC, E, M>(st, oa, ob, fa0, fb0, fa1, fb1, part, bmask);
-#pragma unroll
-        for (int i = 0; i < CC::NBM; ++i)
-#pragma unroll
-          for (int j = 0; j < CC::NBN; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              a[i][j][q] += part[i][j][q];
-              part[i][j][q] = 0.f;
-            }
       } else {
         slab_body<CC, E, M>(st, oa, ob, fa0, fb0, fa1, fb1, a, bmask);
       }
@@ -986,7 +978,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
   if (!zero) {
     using T = BoolTag<true>;
     using F = BoolTag<false>;
-    if constexpr (HSPLIT && STAGE != ST_BX) {
+    if constexpr (STAGE != ST_BX) {
       if (hfast) {
         // the 64 x 64 pieces' accumulators are acc[0..1][*]
         auto& acc2 = reinterpret_cast<f32x16(&)[HalfCfg<C>::NBM][C::NBN]>(acc);
@@ -1022,7 +1014,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
     out_r = out_t;
     rows_needed = ti != tj;  // a diagonal tile is complete with one store
   } else {
-    out_t = TRB ? nullptr : reinterpret_cast<E*>(args.ws + d.xt_off[args.pin ^ 1]);
     out_r = reinterpret_cast<E*>(args.ws + d.x_off[args.pin ^ 1]);
     ld_r = np;
   }
@@ -1049,19 +1040,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] *= mul;
   if (STAGE == ST_BX && args.last) {
-    const PtrEntry pe = args.ptrs[d.index];
-    const float lrs = update_lr(args.lr, d.rows, d.cols);
-    if (d.param_dtype == MUON_BF16) {
-      if (d.transposed)
-        apply_via_lds<C, true, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
-      else
-        apply_via_lds<C, false, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
-    } else {
-      if (d.transposed)
-        apply_via_lds<C, true, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
-      else
-        apply_via_lds<C, false, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
-    }
+    apply_update_tile<C>(acc, region, args, d, row0, col0, lane);
   } else if (masked) {  // square outputs only
     if (dlive) {
       store_t_via_lds<C, E, true>(acc, region, out_t, mp, row0, col0, lane, bmask);
@@ -1074,22 +1053,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void ns_gemm_kernel(GemmArgs args) 
 }
 
 // One launch of one kernel instantiation.
-template <typename E, int TILE, int WGM, int WGN, int STAGE, bool PAD>
+template <typename E, int STAGE, bool PAD>
 int launch_one(unsigned nblocks, const GemmArgs& g, hipStream_t st) {
-  hipLaunchKernelGGL((ns_gemm_kernel<E, TILE, WGM, WGN, STAGE, PAD>), dim3(nblocks), dim3(WGM * WGN * 64), 0, st, g);
+  hipLaunchKernelGGL((ns_gemm_kernel<E, STAGE, PAD>), dim3(nblocks), dim3(512), 0, st, g);
   return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-// Any stage of one class.
-template <typename E, int TILE, int WGM, int WGN, bool PAD = false>
-int launch_stage(int32_t stage, unsigned nblocks, const GemmArgs& g, hipStream_t st) {
-  switch (stage) {
-    case ST_GRAM: return launch_one<E, TILE, WGM, WGN, ST_GRAM, PAD>(nblocks, g, st);
-    case ST_POLY: return launch_one<E, TILE, WGM, WGN, ST_POLY, PAD>(nblocks, g, st);
-    case ST_BX: return launch_one<E, TILE, WGM, WGN, ST_BX, PAD>(nblocks, g, st);
-    case ST_SYM: return launch_one<E, TILE, WGM, WGN, ST_SYM, PAD>(nblocks, g, st);
-    default: return -1;
-  }
 }
 
 }  // namespace

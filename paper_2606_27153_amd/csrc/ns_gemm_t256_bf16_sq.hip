@@ -8,14 +8,14 @@ namespace muon {
 int launch_t256_bf16_sq(bool padded, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st) {
   switch (stage) {
     case ST_GRAM:
-      return padded ? launch_one<__bf16, 256, 2, 4, ST_GRAM, true>(grid, g, st)
-                    : launch_one<__bf16, 256, 2, 4, ST_GRAM, false>(grid, g, st);
+      return padded ? launch_one<__bf16, ST_GRAM, true>(grid, g, st)
+                    : launch_one<__bf16, ST_GRAM, false>(grid, g, st);
     case ST_POLY:
-      return padded ? launch_one<__bf16, 256, 2, 4, ST_POLY, true>(grid, g, st)
-                    : launch_one<__bf16, 256, 2, 4, ST_POLY, false>(grid, g, st);
+      return padded ? launch_one<__bf16, ST_POLY, true>(grid, g, st)
+                    : launch_one<__bf16, ST_POLY, false>(grid, g, st);
     case ST_SYM:
-      return padded ? launch_one<__bf16, 256, 2, 4, ST_SYM, true>(grid, g, st)
-                    : launch_one<__bf16, 256, 2, 4, ST_SYM, false>(grid, g, st);
+      return padded ? launch_one<__bf16, ST_SYM, true>(grid, g, st)
+                    : launch_one<__bf16, ST_SYM, false>(grid, g, st);
     default: return -1;  // B*X has its own translation unit
   }
 }

@@ -5,8 +5,8 @@
 namespace muon {
 
 int launch_t256_f16_bx(bool padded, unsigned grid, const GemmArgs& g, hipStream_t st) {
-  return padded ? launch_one<_Float16, 256, 2, 4, ST_BX, true>(grid, g, st)
-                : launch_one<_Float16, 256, 2, 4, ST_BX, false>(grid, g, st);
+  return padded ? launch_one<_Float16, ST_BX, true>(grid, g, st)
+                : launch_one<_Float16, ST_BX, false>(grid, g, st);
 }
 
 }  // namespace muon

@@ -1,0 +1,16 @@
+// The fp16 small-tile kernels, every stage (see ns_gemm.h for why they have a
+// translation unit of their own).
+#include "ns_tile_kernel.h"
+
+namespace muon {
+
+int launch_tile_f16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st) {
+  switch (exec) {
+    case EX_128_RING3: return launch_tile<_Float16, 128, 3>(stage, grid, g, st);
+    case EX_128_RING2: return launch_tile<_Float16, 128, 2>(stage, grid, g, st);
+    case EX_64_RING3: return launch_tile<_Float16, 64, 3>(stage, grid, g, st);
+    default: return -1;
+  }
+}
+
+}  // namespace muon

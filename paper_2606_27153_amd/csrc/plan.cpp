@@ -8,6 +8,7 @@
 // are advanced together instead of each paying a launch).
 #include <algorithm>
 #include <cmath>
+#include <functional>
 #include <map>
 #include <tuple>
 
@@ -158,6 +159,94 @@ void interleave_units(std::vector<TileEntry>& out, const std::vector<std::vector
     }
     out.push_back(q[size_t(x)][pos[size_t(x)]++]);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Which tile runs a launch.
+//
+// A launch's time is set by its slowest compute unit, so one with fewer
+// 256 tiles than the chip has CUs (a few layers, a single weight) leaves
+// CUs idle, and one with a little more than a multiple of 256 tiles runs a
+// nearly empty last round.  exec_tile estimates the launch's time on every
+// tile that divides the group's padding and takes the shortest:
+// tiles are dealt in list order to 256 * occ slots, each as soon as one is
+// free, and a tile takes `over` + slabs * slab time, the latter growing from
+// `alone` (one block on a CU) to `full` (every slot of the CU busy).  The
+// constants are fitted to launches of 1 to 16 matrices of 256 x 1024 to
+// 2048 x 5632 on each tile (MI355X).  For a single 2048 x 5632 bf16 matrix the
+// launches took, on 256 / 128 / 64 tiles: Gram 122 / 54 / 57 us, polynomial
+// 54 / 35 / 27, B*X 57 / 74 / 87; for four of them 133 / 154 / 180, 56 / 74 /
+// 74, 176 / 224 / 320.  The 64 tile reads twice the 128 tile's and four times
+// the 256 tile's LDS and L2 bytes per flop, which is why it loses as soon as
+// the chip is full.
+// ---------------------------------------------------------------------------
+struct ExecModel {
+  int32_t tile, occ;          // output tile, blocks per CU
+  double start, over;         // us per launch and per tile
+  double alone, full;         // us per 128-byte K slab of one tile
+};
+constexpr int64_t kCus = 256;
+constexpr ExecModel kExec16[EX_COUNT] = {{256, 1, 0.0, 9.5, 1.25, 1.50},
+                                         {128, 2, 2.0, 4.0, 0.74, 1.15},
+                                         {128, 1, 2.0, 4.0, 0.54, 0.62},
+                                         {64, 3, 5.0, 0.7, 0.29, 0.74}};
+// fp32: the matrix cores bound a slab (64 or 16 32x32x2 MFMAs per wave)
+constexpr ExecModel kExec32[EX_COUNT] = {{0, 0, 0, 0, 0, 0},
+                                         {128, 2, 2.0, 4.0, 1.95, 3.80},
+                                         {0, 0, 0, 0, 0, 0},
+                                         {64, 3, 5.0, 0.7, 0.48, 1.35}};
+// launches of more class tiles than this are left on them: the chip is full
+// and the last round matters little
+constexpr int64_t kExecMaxTiles = 4 * kCus;
+
+struct TileLoad {
+  int64_t m_pad, n_pad;   // n_pad = 0: a symmetric output (lower tiles)
+  int64_t slabs;
+};
+
+int64_t tile_count(const TileLoad& t, int64_t tile) {
+  const int64_t a = t.m_pad / tile, b = t.n_pad / tile;
+  return t.n_pad ? a * b : a * (a + 1) / 2;
+}
+
+// Estimated time of a launch over these matrices on one kernel.
+double exec_time(const std::vector<TileLoad>& loads, const ExecModel& e) {
+  int64_t total = 0;
+  for (const TileLoad& t : loads) total += tile_count(t, e.tile);
+  const double share = e.occ == 1 ? double(std::min(total, kCus)) / double(kCus)
+                                  : double(std::min(std::max<int64_t>(total - kCus, 0), kCus * (e.occ - 1))) /
+                                        double(kCus * (e.occ - 1));
+  const double slab = e.alone + (e.full - e.alone) * share;
+  std::vector<double> heap(size_t(std::min(total, kCus * e.occ)), 0.0);  // min-heap of slot end times
+  double end = 0;
+  for (const TileLoad& t : loads) {
+    const double dt = e.over + double(t.slabs) * slab;
+    for (int64_t i = tile_count(t, e.tile); i > 0; --i) {
+      std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+      heap.back() += dt;
+      end = std::max(end, heap.back());
+      std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+    }
+  }
+  return e.start + end;
+}
+
+// The kernel for a launch whose class tile is `tile` and whose class lists
+// hold `class_tiles` tiles.
+int32_t exec_tile(const std::vector<TileLoad>& loads, int32_t tile, bool fp32, int64_t class_tiles) {
+  int32_t best = tile == 256 ? EX_256 : tile == 128 ? EX_128_RING2 : EX_64_RING3;
+  if (class_tiles > kExecMaxTiles) return best;
+  double best_t = 0;
+  for (int32_t x = 0; x < EX_COUNT; ++x) {
+    const ExecModel& e = fp32 ? kExec32[x] : kExec16[x];
+    if (e.tile == 0 || e.tile > tile) continue;
+    const double t = exec_time(loads, e);
+    if (best_t == 0 || t < best_t) {
+      best = x;
+      best_t = t;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -482,6 +571,48 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
       cl.strip_full_off = int64_t(p.h_tiles.size());
       cl.n_strip_full = int32_t(strip_full.size());
       p.h_tiles.insert(p.h_tiles.end(), strip_full.begin(), strip_full.end());
+      // the tiles each kind of launch runs on
+      std::vector<TileLoad> lg, ls, lf;
+      for (int32_t s = 0; s < w.count; ++s) {
+        const MatHost& h = p.mats[size_t(p.order[size_t(w.first + s)])];
+        if (h.kclass != kc || h.gram != gram) continue;
+        const int64_t bk = kClasses[kc].fp32 ? 32 : 64;
+        const int64_t sm = (h.m + bk - 1) / bk, sn = (h.n + bk - 1) / bk;
+        lg.push_back(TileLoad{h.m_pad, 0, sn});
+        ls.push_back(TileLoad{h.m_pad, 0, sm});
+        lf.push_back(TileLoad{h.m_pad, h.n_pad, sm});
+      }
+      std::map<std::pair<int64_t, bool>, StageRun> small;  // (tile, full) -> list built so far
+      auto stage_run = [&](const std::vector<TileLoad>& loads, bool is_full) {
+        const int64_t own = is_full ? cl.n_full + cl.n_strip_full : cl.n_lower;
+        StageRun r{exec_tile(loads, int32_t(tile), kClasses[kc].fp32 != 0, own), is_full ? cl.full_off : cl.lower_off,
+                   is_full ? cl.n_full : cl.n_lower};
+        const int64_t t = kExec16[r.exec].tile;
+        if (t == tile) return r;
+        StageRun& list = small[{t, is_full}];
+        if (list.n == 0) {
+          std::vector<std::vector<TileEntry>> u;
+          std::vector<TileEntry> out;
+          for (int32_t s = 0; s < w.count; ++s) {
+            const MatHost& h = p.mats[size_t(p.order[size_t(w.first + s)])];
+            if (h.kclass != kc || h.gram != gram) continue;
+            if (is_full)
+              full_units(u, w.first + s, h.m_pad / t, h.n_pad / t);
+            else
+              lower_units(u, w.first + s, h.m_pad / t);
+          }
+          interleave_units(out, u);
+          list.off = int64_t(p.h_tiles.size());
+          list.n = int32_t(out.size());
+          p.h_tiles.insert(p.h_tiles.end(), out.begin(), out.end());
+        }
+        r.off = list.off;
+        r.n = list.n;
+        return r;
+      };
+      cl.run_gram = stage_run(lg, false);
+      cl.run_square = stage_run(ls, false);
+      cl.run_full = stage_run(lf, true);
       w.launches.push_back(cl);
     }
   }

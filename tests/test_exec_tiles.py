@@ -1,0 +1,77 @@
+"""Launches that would leave much of the chip idle run on smaller tiles than
+their class's.  Host: the lists they run on cover every output exactly once.
+GPU: an element's value does not depend on the tile that computed it -- a
+matrix on its own (small tiles) and the same matrix among enough others to
+fill the chip (256 tiles with their half tiles and edge strips, or the class
+tile) give bitwise the same W, M and O."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_27153_amd.optim import MuonPlan
+from paper_2606_27153_amd.workloads import WORKLOAD_KEYS, custom_workload, get_workload, make_grads, make_state
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def lists_check(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("exec") / "exec_lists_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "exec_lists_check.cpp"),
+                    os.path.join(ROOT, "paper_2606_27153_amd", "csrc", "plan.cpp"), "-o", str(exe)], check=True)
+    return str(exe)
+
+
+def _run(exe, shapes, precision):
+    out = subprocess.run([exe, str(precision)], input="\n".join(f"{r} {c}" for r, c in shapes), capture_output=True,
+                         text=True)
+    assert out.returncode == 0 and out.stdout.startswith("OK"), out.stdout + out.stderr
+    return [int(v) for v in out.stdout.split()[1:]]
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_lists_cover_outputs(lists_check, precision):
+    rng = np.random.default_rng(7)
+    used = np.zeros(4, int)
+    for n in (1, 2, 3, 5, 9, 17):
+        for _ in range(6):
+            shapes = [(int(rng.integers(1, 2600)), int(rng.integers(1, 2600))) for _ in range(n)]
+            used += _run(lists_check, shapes, precision)
+    for r, c in ((1, 1), (64, 64), (65, 65), (256, 256), (257, 257), (384, 385), (2048, 5632), (4096, 14336)):
+        used += _run(lists_check, [(r, c)], precision)
+    # every kernel the precision has is chosen somewhere
+    assert used[1] and used[3] and (precision == 1 or (used[0] and used[2])), used
+    for key in WORKLOAD_KEYS:
+        _run(lists_check, [(m.rows, m.cols) for m in get_workload(key).matrices], precision)
+
+
+# one matrix shape, and how many of it leave the small tiles: one-tile and
+# two-tile squares, half tiles and edge strips on both sides, a tall and a wide
+# Gram-space matrix, odd columns, the 128 and 64 classes
+SHAPES = [((256, 256), 300), ((512, 512), 150), ((640, 640), 120), ((384, 1100), 150), ((1152, 385), 150),
+          ((300, 301), 200), ((130, 700), 300), ((96, 520), 400), ((40, 200), 900)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["bf16", "fp16", "fp32"])
+@pytest.mark.parametrize("shape,many", SHAPES, ids=[f"{s[0]}x{s[1]}" for s, _ in SHAPES])
+def test_value_does_not_depend_on_the_tile(shape, many, precision):
+    dev = "cuda:0"
+    got = []
+    for n in (1, many):
+        wl = custom_workload([shape] * n, seed=71)
+        plan = MuonPlan([(m.rows, m.cols, m.param, m.grad) for m in wl.matrices], precision=precision)
+        params, moms = make_state(torch, wl, dev)
+        grads = make_grads(torch, wl, 0, dev)
+        outs = [torch.full(shape, float("nan"), device=dev)] + [None] * (n - 1)
+        plan.step(params, grads, moms, lr=0.02, momentum=0.95, weight_decay=0.01, ns_steps=5, update_out=outs)
+        torch.cuda.synchronize()
+        got.append((params[0], moms[0], outs[0]))
+        plan.close()
+    for a, b in zip(*got):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, b)
