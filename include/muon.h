@@ -221,10 +221,14 @@ MUON_API muon_status muon_plan_matrix_info(muon_plan plan, int32_t index, muon_m
  *
  * The call only enqueues work on hip_stream; it never allocates and never
  * waits for the stream.  The plan keeps a device copy of the pointer arrays:
- * when they differ from the previous call's, the new table is written into
- * the next slot of a pinned host ring the plan owns (8 slots) and copied to
- * the device on hip_stream ahead of the kernels.  The host waits only when
- * that slot's copy from 8 refreshes earlier has not yet run on the GPU.
+ * when they differ from the previous call's, the new table goes to the device
+ * on hip_stream ahead of the kernels: up to 112 matrices in the arguments of
+ * the momentum kernel, more from the next slot of a pinned host ring the plan owns
+ * (8 slots), where the host waits only when that slot's copy from 8 refreshes
+ * earlier has not yet run on the GPU.
+ * Groups of matrices (kernel class and iteration form) may run side by side
+ * on up to 3 streams the plan owns, forked from hip_stream after the momentum
+ * pass and joined back to it: to the caller all of it is work on hip_stream.
  * Successive steps on one plan must be ordered on the GPU (one stream, or
  * ordered by the caller): each refresh overwrites the device table the
  * previous step's kernels read.

@@ -90,19 +90,41 @@ muon_status upload_tables(muon::Plan& p) {
   if (e == hipSuccess && !p.h_tiles.empty())
     e = hipMemcpy(p.d_tiles, p.h_tiles.data(), p.h_tiles.size() * sizeof(TileEntry), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "upload of plan tables");
-  // the pinned ring the step refreshes the pointer table from
-  e = hipHostMalloc(reinterpret_cast<void**>(&p.h_ring), size_t(Plan::kRing) * p.mats.size() * sizeof(PtrEntry),
-                    hipHostMallocDefault);
+  // the pinned ring the step refreshes a long pointer table from
+  const int ring = p.mats.size() > size_t(kPtrChunk) ? Plan::kRing : 0;
+  if (ring)
+    e = hipHostMalloc(reinterpret_cast<void**>(&p.h_ring), size_t(ring) * p.mats.size() * sizeof(PtrEntry),
+                      hipHostMallocDefault);
   if (e != hipSuccess) {
     p.h_ring = nullptr;
     return e == hipErrorOutOfMemory ? fail(MUON_ERR_OUT_OF_MEMORY, "hipHostMalloc of the pointer ring failed")
                                     : hip_fail(e, "hipHostMalloc of the pointer ring");
   }
-  for (int k = 0; k < Plan::kRing; ++k) {
+  for (int k = 0; k < ring; ++k) {
     hipEvent_t ev = nullptr;
     e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreateWithFlags");
     p.ring_events[k] = ev;
+  }
+  int aside = 0;
+  for (const auto& w : p.waves) {
+    int c = 0;
+    for (int i = 0; i < int(w.launches.size()); ++i)
+      c += i != main_group_of(w) && side_group(w.launches[size_t(i)]) ? 1 : 0;
+    aside = std::max(aside, c);
+  }
+  for (; p.n_side < std::min(aside, Plan::kSide); ++p.n_side) {
+    hipStream_t side = nullptr;
+    hipEvent_t ev = nullptr;
+    e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
+    p.side[p.n_side] = side;
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    p.join_events[p.n_side] = ev;
+    if (e == hipSuccess && !p.fork_event) {
+      e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+      if (e == hipSuccess) p.fork_event = ev;
+    }
+    if (e != hipSuccess) return hip_fail(e, "creating the plan's side streams");
   }
   return MUON_OK;
 }
@@ -117,6 +139,14 @@ hipError_t release_device(muon::Plan& p) {
     if (p.ring_events[k]) keep(hipEventDestroy(hipEvent_t(p.ring_events[k])));
     p.ring_events[k] = nullptr;
   }
+  for (int k = 0; k < muon::Plan::kSide; ++k) {
+    if (p.join_events[k]) keep(hipEventDestroy(hipEvent_t(p.join_events[k])));
+    if (p.side[k]) keep(hipStreamDestroy(hipStream_t(p.side[k])));
+    p.join_events[k] = p.side[k] = nullptr;
+  }
+  if (p.fork_event) keep(hipEventDestroy(hipEvent_t(p.fork_event)));
+  p.fork_event = nullptr;
+  p.n_side = 0;
   if (p.h_ring) keep(hipHostFree(p.h_ring));
   p.h_ring = nullptr;
   if (p.d_block) keep(hipFree(p.d_block));
@@ -257,24 +287,26 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
       return fail(MUON_ERR_INVALID_ARG,
                   "buffer addresses differ from the previous step's while the stream is being captured; "
                   "step once on these buffers before the capture");
-    const int k = p.ring_next;
-    if (p.ring_busy[k]) {
-      e = hipEventSynchronize(hipEvent_t(p.ring_events[k]));
-      if (e != hipSuccess) return hip_fail(e, "waiting for a pointer-ring slot");
-    }
-    PtrEntry* slot = p.h_ring + size_t(k) * n;
-    for (size_t i = 0; i < n; ++i) {
-      slot[i] = PtrEntry{params[i], grads[i], static_cast<float*>(momentum[i]), update_out ? update_out[i] : nullptr};
-      p.h_ptrs[i] = slot[i];
-    }
     p.ptrs_valid = false;
-    e = hipMemcpyAsync(p.d_ptrs, slot, n * sizeof(PtrEntry), hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess) e = hipEventRecord(hipEvent_t(p.ring_events[k]), hs);
-    if (e != hipSuccess) return hip_fail(e, "upload of buffer pointers");
-    p.ring_busy[k] = true;
-    p.ring_next = (k + 1) % Plan::kRing;
-    p.ptrs_valid = true;
+    for (size_t i = 0; i < n; ++i)
+      p.h_ptrs[i] =
+          PtrEntry{params[i], grads[i], static_cast<float*>(momentum[i]), update_out ? update_out[i] : nullptr};
+    if (n > size_t(kPtrChunk)) {
+      const int k = p.ring_next;
+      if (p.ring_busy[k]) {
+        e = hipEventSynchronize(hipEvent_t(p.ring_events[k]));
+        if (e != hipSuccess) return hip_fail(e, "waiting for a pointer-ring slot");
+      }
+      PtrEntry* slot = p.h_ring + size_t(k) * n;
+      std::copy(p.h_ptrs.begin(), p.h_ptrs.end(), slot);
+      e = hipMemcpyAsync(p.d_ptrs, slot, n * sizeof(PtrEntry), hipMemcpyHostToDevice, hs);
+      if (e == hipSuccess) e = hipEventRecord(hipEvent_t(p.ring_events[k]), hs);
+      if (e != hipSuccess) return hip_fail(e, "upload of buffer pointers");
+      p.ring_busy[k] = true;
+      p.ring_next = (k + 1) % Plan::kRing;
+    }
   }
+  const bool with_table = changed && n <= size_t(kPtrChunk);
 
   StepScalars s{};
   s.lr = lr;
@@ -285,8 +317,9 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
   s.nesterov = nesterov;
   s.ns_steps = ns_steps;
   char* ws = static_cast<char*>(workspace);
-  // Runs one launch, bracketed by timing events when timing is enabled.
-  auto run = [&](int32_t kind, int32_t kclass, double flops, double bytes, auto&& launch) -> hipError_t {
+  // Runs one launch on `on`, bracketed by timing events when timing is enabled.
+  auto run = [&](int32_t kind, int32_t kclass, double flops, double bytes, hipStream_t on,
+                 auto&& launch) -> hipError_t {
     size_t ev = 0;
     if (timing) {
       ev = p.records.size() * 2;
@@ -296,7 +329,7 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
         if (er != hipSuccess) return er;
         p.events.push_back(e);
       }
-      hipError_t er = hipEventRecord(hipEvent_t(p.events[ev]), hs);
+      hipError_t er = hipEventRecord(hipEvent_t(p.events[ev]), on);
       if (er != hipSuccess) return er;
     }
     if (launch()) {
@@ -304,46 +337,37 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
       return er == hipSuccess ? hipErrorLaunchFailure : er;
     }
     if (timing) {
-      hipError_t er = hipEventRecord(hipEvent_t(p.events[ev + 1]), hs);
+      hipError_t er = hipEventRecord(hipEvent_t(p.events[ev + 1]), on);
       if (er != hipSuccess) return er;
       p.records.push_back(TimingRecord{kind, kclass, flops, bytes, ev});
     }
     return hipSuccess;
   };
-  for (const WaveHost& w : p.waves) {
-    e = run(MUON_KERNEL_MOMENTUM, -1, 0.0, w.bytes_momentum, [&] { return launch_momentum(p, w, ws, s, stream); });
-    if (e != hipSuccess) return hip_fail(e, "momentum kernel launch");
-    e = run(MUON_KERNEL_FINALIZE, -1, 0.0, 0.0, [&] { return launch_finalize(p, w, ws, s, stream); });
-    if (e != hipSuccess) return hip_fail(e, "finalize kernel launch");
-    auto gemm = [&](const ClassLaunch& cl, int32_t stage, int32_t kind, const GemmStep& g) {
+  // Every NS launch of one group (kernel class and form) of a wave, in order
+  // on one stream.
+  auto run_group = [&](const WaveHost& w, const ClassLaunch& cl, hipStream_t on) -> hipError_t {
+    auto gemm = [&](int32_t stage, int32_t kind, const GemmStep& g) {
       const double fl = (kind == MUON_KERNEL_GRAM ? cl.flops_gram : kind == MUON_KERNEL_BX ? cl.flops_bx : cl.flops_poly) *
                         (g.pair ? 2.0 : 1.0);
-      return run(kind, cl.kclass, fl, 0.0, [&] { return launch_ns_gemm(p, w, cl, stage, g, ws, s, stream); });
+      return run(kind, cl.kclass, fl, 0.0, on, [&] { return launch_ns_gemm(p, w, cl, stage, g, ws, s, on); });
     };
-    // Eq. 2: per step A = s^2 X X^T, B = b A + c A A, X' = s (a X + B X),
-    // with step it's (a, b, c).  With c = 0 (a cubic step) the Gram stage
-    // writes B = b A itself.
-    for (int32_t it = 0; it < ns_steps; ++it) {
-      const int32_t first = it == 0, pin = it & 1, last = it == ns_steps - 1;
-      const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
-      const bool cubic = c == 0.f;
-      for (const ClassLaunch& cl : w.launches) {
-        if (cl.gram) continue;
-        e = gemm(cl, ST_GRAM, MUON_KERNEL_GRAM,
-                 GemmStep{first, pin, last, SQ_A, SQ_A, cubic ? SQ_B : SQ_A, 0.f, 0.f, cubic ? b : 1.f});
-        if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
+    hipError_t er = hipSuccess;
+    if (!cl.gram) {
+      // Eq. 2: per step A = s^2 X X^T, B = b A + c A A, X' = s (a X + B X),
+      // with step it's (a, b, c).  With c = 0 (a cubic step) the Gram stage
+      // writes B = b A itself.
+      for (int32_t it = 0; it < ns_steps && er == hipSuccess; ++it) {
+        const int32_t first = it == 0, pin = it & 1, last = it == ns_steps - 1;
+        const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
+        const bool cubic = c == 0.f;
+        er = gemm(ST_GRAM, MUON_KERNEL_GRAM,
+                  GemmStep{first, pin, last, SQ_A, SQ_A, cubic ? SQ_B : SQ_A, 0.f, 0.f, cubic ? b : 1.f});
+        if (er == hipSuccess && !cubic)
+          er = gemm(ST_POLY, MUON_KERNEL_POLY, GemmStep{first, pin, last, SQ_A, SQ_A, SQ_B, b / c, 0.f, c});
+        if (er == hipSuccess)
+          er = gemm(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, SQ_B, SQ_B, SQ_B, a, 0.f, 1.f});
       }
-      if (!cubic)
-        for (const ClassLaunch& cl : w.launches) {
-          if (cl.gram) continue;
-          e = gemm(cl, ST_POLY, MUON_KERNEL_POLY, GemmStep{first, pin, last, SQ_A, SQ_A, SQ_B, b / c, 0.f, c});
-          if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
-        }
-      for (const ClassLaunch& cl : w.launches) {
-        if (cl.gram) continue;
-        e = gemm(cl, ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, SQ_B, SQ_B, SQ_B, a, 0.f, 1.f});
-        if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
-      }
+      return er;
     }
     // Gram space (Eq. 4), in segments of at most gram_restart steps.  A
     // segment starting from X (X0 = s u in the first) forms G = X X^T; per
@@ -355,45 +379,90 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
     // only need P_i, so they share one launch.  In segments of at most two
     // steps R lives in B's memory and the second Q in A's (gram_shares_buffers):
     // this order writes each only after the last read of what it replaces.
-    for (const ClassLaunch& cl : w.launches) {
-      if (!cl.gram) continue;
-      int32_t pin = 0;
-      for (int32_t s0 = 0; s0 < ns_steps; s0 += p.gram_restart) {
-        const int32_t len = std::min(p.gram_restart, ns_steps - s0);
-        const int32_t first = s0 == 0, last = s0 + len == ns_steps;
-        e = gemm(cl, ST_GRAM, MUON_KERNEL_GRAM, GemmStep{first, pin, 0, SQ_A, SQ_A, SQ_A, 0.f, 0.f, 1.f});
-        if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
-        for (int32_t j = 0; j < len; ++j) {
-          const int32_t it = s0 + j;
-          const int32_t pbuf = j == 0 ? SQ_Q0 : SQ_B;
-          const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
-          e = gemm(cl, ST_POLY, MUON_KERNEL_POLY, GemmStep{0, 0, 0, SQ_A, SQ_A, pbuf, b / c, a / c, c});
-          const GemmStep qu{0, 0, 0, SQ_B, (j - 1) & 1 ? SQ_Q1 : SQ_Q0, j & 1 ? SQ_Q1 : SQ_Q0, 0.f, 0.f, 1.f};
-          GemmStep gr{0, 0, 0, SQ_A, pbuf, SQ_R, 0.f, 0.f, 1.f};
-          const bool need_qu = j > 0, need_gr = j + 1 < len;
-          if (e == hipSuccess && need_qu && need_gr) {
-            gr.pair = 1;
-            gr.l2 = qu.l;
-            gr.r2 = qu.r;
-            gr.out2 = qu.out;
-            e = gemm(cl, ST_SYM, MUON_KERNEL_SYMM, gr);
-          } else if (e == hipSuccess && (need_qu || need_gr)) {
-            e = gemm(cl, ST_SYM, MUON_KERNEL_SYMM, need_qu ? qu : gr);
-          }
-          if (e == hipSuccess && need_gr)
-            e = gemm(cl, ST_SYM, MUON_KERNEL_SYMM, GemmStep{0, 0, 0, pbuf, SQ_R, SQ_A, 0.f, 0.f, 1.f});
-          if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
+    int32_t pin = 0;
+    for (int32_t s0 = 0; s0 < ns_steps && er == hipSuccess; s0 += p.gram_restart) {
+      const int32_t len = std::min(p.gram_restart, ns_steps - s0);
+      const int32_t first = s0 == 0, last = s0 + len == ns_steps;
+      er = gemm(ST_GRAM, MUON_KERNEL_GRAM, GemmStep{first, pin, 0, SQ_A, SQ_A, SQ_A, 0.f, 0.f, 1.f});
+      for (int32_t j = 0; j < len && er == hipSuccess; ++j) {
+        const int32_t it = s0 + j;
+        const int32_t pbuf = j == 0 ? SQ_Q0 : SQ_B;
+        const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
+        er = gemm(ST_POLY, MUON_KERNEL_POLY, GemmStep{0, 0, 0, SQ_A, SQ_A, pbuf, b / c, a / c, c});
+        const GemmStep qu{0, 0, 0, SQ_B, (j - 1) & 1 ? SQ_Q1 : SQ_Q0, j & 1 ? SQ_Q1 : SQ_Q0, 0.f, 0.f, 1.f};
+        GemmStep gr{0, 0, 0, SQ_A, pbuf, SQ_R, 0.f, 0.f, 1.f};
+        const bool need_qu = j > 0, need_gr = j + 1 < len;
+        if (er == hipSuccess && need_qu && need_gr) {
+          gr.pair = 1;
+          gr.l2 = qu.l;
+          gr.r2 = qu.r;
+          gr.out2 = qu.out;
+          er = gemm(ST_SYM, MUON_KERNEL_SYMM, gr);
+        } else if (er == hipSuccess && (need_qu || need_gr)) {
+          er = gemm(ST_SYM, MUON_KERNEL_SYMM, need_qu ? qu : gr);
         }
-        const int32_t qk = (len - 1) & 1 ? SQ_Q1 : SQ_Q0;
-        e = gemm(cl, ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, qk, qk, qk, 0.f, 0.f, 1.f});
-        if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
-        pin ^= 1;
+        if (er == hipSuccess && need_gr)
+          er = gemm(ST_SYM, MUON_KERNEL_SYMM, GemmStep{0, 0, 0, pbuf, SQ_R, SQ_A, 0.f, 0.f, 1.f});
       }
+      const int32_t qk = (len - 1) & 1 ? SQ_Q1 : SQ_Q0;
+      if (er == hipSuccess)
+        er = gemm(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, qk, qk, qk, 0.f, 0.f, 1.f});
+      pin ^= 1;
     }
+    return er;
+  };
+  // The groups of one wave.  Each is a chain of 15 or 17 dependent launches
+  // (k = 5) that touches its own matrices only, so the chains run side by side:
+  // one launch's last round, or a launch too small for the chip, then leaves
+  // no CU idle that another chain could use.  The group with the most work
+  // stays on the caller's stream; those that do not fill the chip for long
+  // (side_group) are enqueued first, on the plan's side streams, and joined
+  // back before the wave ends.  With launch
+  // timing on everything runs on the caller's stream, so that a launch's events
+  // time that launch alone.
+  auto run_groups = [&](const WaveHost& w) -> hipError_t {
+    const int n = int(w.launches.size());
+    const int main_group = main_group_of(w);
+    auto aside = [&](int i) { return !timing && i != main_group && p.n_side > 0 && side_group(w.launches[size_t(i)]); };
+    bool any = false;
+    for (int i = 0; i < n; ++i) any = any || aside(i);
+    hipError_t er = any ? hipEventRecord(hipEvent_t(p.fork_event), hs) : hipSuccess;
+    int used = 0, next = 0;
+    for (int i = 0; i < n && er == hipSuccess; ++i) {
+      if (!aside(i)) continue;
+      hipStream_t on = hipStream_t(p.side[next]);
+      if (next >= used) {
+        er = hipStreamWaitEvent(on, hipEvent_t(p.fork_event), 0);
+        if (er != hipSuccess) break;
+        used = next + 1;
+      }
+      er = run_group(w, w.launches[size_t(i)], on);
+      next = (next + 1) % p.n_side;
+    }
+    for (int i = 0; i < n && er == hipSuccess; ++i)
+      if (!aside(i)) er = run_group(w, w.launches[size_t(i)], hs);
+    // joined on an error as well: nothing outlives the call's place in the stream
+    for (int k = 0; k < used; ++k) {
+      hipError_t ej = hipEventRecord(hipEvent_t(p.join_events[k]), hipStream_t(p.side[k]));
+      if (ej == hipSuccess) ej = hipStreamWaitEvent(hs, hipEvent_t(p.join_events[k]), 0);
+      if (er == hipSuccess) er = ej;
+    }
+    return er;
+  };
+  for (const WaveHost& w : p.waves) {
+    e = run(MUON_KERNEL_MOMENTUM, -1, 0.0, w.bytes_momentum, hs, [&] {
+      return launch_momentum(p, w, ws, s, with_table, stream);
+    });
+    if (e != hipSuccess) return hip_fail(e, "momentum kernel launch");
+    if (&w == &p.waves.back()) p.ptrs_valid = true;  // every entry has been handed over
+    e = run(MUON_KERNEL_FINALIZE, -1, 0.0, 0.0, hs, [&] { return launch_finalize(p, w, ws, s, stream); });
+    if (e != hipSuccess) return hip_fail(e, "finalize kernel launch");
+    e = run_groups(w);
+    if (e != hipSuccess) return hip_fail(e, "NS GEMM launch");
     // With k >= 1 the last B*X launch applied the update (zero-gradient
     // matrices included); with k = 0 the update is O = s*u.
     if (ns_steps == 0) {
-      e = run(MUON_KERNEL_APPLY, -1, 0.0, w.bytes_apply, [&] { return launch_apply(p, w, ws, s, stream); });
+      e = run(MUON_KERNEL_APPLY, -1, 0.0, w.bytes_apply, hs, [&] { return launch_apply(p, w, ws, s, stream); });
       if (e != hipSuccess) return hip_fail(e, "apply kernel launch");
     }
   }

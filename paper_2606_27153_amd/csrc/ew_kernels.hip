@@ -18,6 +18,8 @@
 // matrix by binary search over the wave's tile prefix.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ew_common.h"
 #include "muon_internal.h"
 
@@ -53,10 +55,22 @@ __device__ inline void store_x4(char* buf, int64_t idx, int x_f32, int x_f16, co
   }
 }
 
+// A pointer table of up to kPtrChunk matrices, handed over by value: the
+// entries travel with the momentum launch itself.
+struct PtrChunk {
+  PtrEntry e[kPtrChunk];
+};
+static_assert(sizeof(PtrChunk) <= 3600, "fits the 4 KB of kernel arguments");
+struct NoChunk {};
+
+// CHUNK = PtrChunk: the buffers moved since the last step; their pointers are
+// read from the arguments, and each matrix's first block writes its entry to
+// the device table, which the later kernels read.
+template <class CHUNK>
 __global__ __launch_bounds__(256) void momentum_kernel(const MatDev* __restrict__ mats,
                                                        const int32_t* __restrict__ prefix, int count,
-                                                       const PtrEntry* __restrict__ ptrs, char* __restrict__ ws,
-                                                       float mu, int nesterov) {
+                                                       PtrEntry* __restrict__ ptrs, char* __restrict__ ws,
+                                                       float mu, int nesterov, CHUNK chunk) {
   __shared__ float tile_t[64][65];
   __shared__ float red[4];
   const int bid = blockIdx.x;
@@ -64,8 +78,14 @@ __global__ __launch_bounds__(256) void momentum_kernel(const MatDev* __restrict_
   const MatDev& d = mats[s];
   const int local = bid - prefix[s];
   const int tr = local / d.ew_tiles_c, tc = local - tr * d.ew_tiles_c;
-  const PtrEntry pe = ptrs[d.index];
   const int t = threadIdx.x;
+  PtrEntry pe;
+  if constexpr (__is_same(CHUNK, PtrChunk)) {
+    pe = chunk.e[d.index];
+    if (local == 0 && t == 0) ptrs[d.index] = pe;
+  } else {
+    pe = ptrs[d.index];
+  }
   if (!pe.grad) {  // no gradient this step: M and X are left alone
     if (t == 0) reinterpret_cast<float*>(ws + d.partial_off)[local] = 0.f;
     return;
@@ -215,9 +235,17 @@ __global__ __launch_bounds__(256) void apply_kernel(const MatDev* __restrict__ m
 
 static int check_launch() { return hipGetLastError() == hipSuccess ? 0 : -1; }
 
-int launch_momentum(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, void* stream) {
-  hipLaunchKernelGGL(momentum_kernel, dim3(unsigned(w.ew_tiles)), dim3(256), 0, hipStream_t(stream),
-                     p.d_mats + w.first, p.d_prefix + w.prefix_off, w.count, p.d_ptrs, ws, s.mu, s.nesterov);
+int launch_momentum(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, bool with_table, void* stream) {
+  if (with_table) {
+    PtrChunk c;
+    std::copy(p.h_ptrs.begin(), p.h_ptrs.end(), c.e);
+    hipLaunchKernelGGL(momentum_kernel<PtrChunk>, dim3(unsigned(w.ew_tiles)), dim3(256), 0, hipStream_t(stream),
+                       p.d_mats + w.first, p.d_prefix + w.prefix_off, w.count, p.d_ptrs, ws, s.mu, s.nesterov, c);
+  } else {
+    hipLaunchKernelGGL(momentum_kernel<NoChunk>, dim3(unsigned(w.ew_tiles)), dim3(256), 0, hipStream_t(stream),
+                       p.d_mats + w.first, p.d_prefix + w.prefix_off, w.count, p.d_ptrs, ws, s.mu, s.nesterov,
+                       NoChunk{});
+  }
   return check_launch();
 }
 

@@ -191,7 +191,8 @@ struct Plan {
   std::vector<PtrEntry> h_ptrs;     // host shadow of d_ptrs
   bool ptrs_valid = false;
   const void* ws_checked = nullptr;  // workspace whose memory was last vetted
-  // Pinned host ring of pointer tables: a step whose buffers moved fills the
+  // Pinned host ring of pointer tables (tables of more than kPtrChunk
+  // matrices): a step whose buffers moved fills the
   // next slot and copies it to d_ptrs on the caller's stream; the slot's
   // event marks when that copy has read it.
   static constexpr int kRing = 8;
@@ -199,6 +200,15 @@ struct Plan {
   void* ring_events[kRing] = {};
   bool ring_busy[kRing] = {};
   int ring_next = 0;
+  // Side streams: the groups of a wave are independent between finalize and
+  // the end of the wave, so all but the largest run on streams of their own,
+  // forked from and joined to the caller's stream by events (run_groups in
+  // api.cpp).  Created with the plan, only as many as its waves can use.
+  static constexpr int kSide = 3;
+  int n_side = 0;
+  void* side[kSide] = {};           // hipStream_t, default priority
+  void* fork_event = nullptr;
+  void* join_events[kSide] = {};
   // this device's static workspace (muon_step_static), null if the lookup
   // failed (static_ws_status holds the hipError_t)
   void* static_ws = nullptr;
@@ -230,6 +240,20 @@ inline bool gram_shares_buffers(const Plan& p, int32_t max_ns_steps) {
   return (p.gram_restart < max_ns_steps ? p.gram_restart : max_ns_steps) <= 2;
 }
 
+// Whether a group of a wave runs on a side stream, next to the wave's largest
+// group (main_group_of), instead of before or after it: when its launches are
+// short of two rounds of 256 tiles.  Measured: a 1B layer (72 tiles beside 114)
+// 1902 -> 1686 us, two MoE layers (144 beside 8076) 32.0 -> 31.5 ms; but four
+// 8B layers (1088 beside 1712) 42.8 -> 43.4 ms, and the 1B and VLA sets gain
+// nothing: launches that fill the chip only take each other's L2.
+inline bool side_group(const ClassLaunch& cl) { return cl.n_lower <= 512; }
+inline int main_group_of(const WaveHost& w) {
+  int best = 0;
+  for (int i = 1; i < int(w.launches.size()); ++i)
+    if (w.launches[size_t(i)].flops_bx > w.launches[size_t(best)].flops_bx) best = i;
+  return best;
+}
+
 // Per-launch arguments shared by the kernel launchers.
 struct StepScalars {
   float lr, mu, wd, decay;  // decay = 1 - lr*wd
@@ -238,7 +262,13 @@ struct StepScalars {
 };
 
 // ew_kernels.hip
-int launch_momentum(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, void* stream);
+// A pointer table of at most kPtrChunk matrices travels in the arguments of the
+// momentum launches (with_table: h_ptrs differs from the device's table), a
+// longer one in a copy from the plan's pinned ring ahead of them.  On the tiny
+// set (8 matrices) with gradients that move every step the copy cost 21 us of
+// a step.
+constexpr int kPtrChunk = 112;
+int launch_momentum(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, bool with_table, void* stream);
 int launch_finalize(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, void* stream);
 int launch_apply(const Plan& p, const WaveHost& w, char* ws, const StepScalars& s, void* stream);
 

@@ -217,11 +217,21 @@ double exec_time(const std::vector<TileLoad>& loads, const ExecModel& e) {
                                   : double(std::min(std::max<int64_t>(total - kCus, 0), kCus * (e.occ - 1))) /
                                         double(kCus * (e.occ - 1));
   const double slab = e.alone + (e.full - e.alone) * share;
-  std::vector<double> heap(size_t(std::min(total, kCus * e.occ)), 0.0);  // min-heap of slot end times
+  const int64_t slots = std::min(total, kCus * e.occ);
+  std::vector<double> heap(size_t(slots), 0.0);  // min-heap of slot end times
   double end = 0;
-  for (const TileLoad& t : loads) {
-    const double dt = e.over + double(t.slabs) * slab;
-    for (int64_t i = tile_count(t, e.tile); i > 0; --i) {
+  for (size_t i = 0; i < loads.size();) {
+    const int64_t slabs = loads[i].slabs;
+    const double dt = e.over + double(slabs) * slab;
+    int64_t n = 0;  // tiles of a run of matrices with the same K
+    for (; i < loads.size() && loads[i].slabs == slabs; ++i) n += tile_count(loads[i], e.tile);
+    // all but the last two rounds of a long run level out over the slots
+    if (n > 2 * slots) {
+      const int64_t rounds = n / slots - 1;
+      for (double& h : heap) h += double(rounds) * dt;
+      n -= rounds * slots;
+    }
+    for (; n > 0; --n) {
       std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
       heap.back() += dt;
       end = std::max(end, heap.back());
