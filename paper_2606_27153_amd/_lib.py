@@ -148,10 +148,7 @@ def check(status: int) -> None:
 
 
 def ptr_array(values):
-    arr = (ctypes.c_void_p * len(values))()
-    for i, v in enumerate(values):
-        arr[i] = v
-    return arr
+    return (ctypes.c_void_p * len(values))(*values)
 
 
 def __getattr__(name):

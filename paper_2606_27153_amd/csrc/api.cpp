@@ -109,9 +109,8 @@ muon_status upload_tables(muon::Plan& p) {
   int aside = 0;
   for (const auto& w : p.waves) {
     int c = 0;
-    for (int i = 0; i < int(w.launches.size()); ++i)
-      c += i != main_group_of(w) && side_group(w.launches[size_t(i)]) ? 1 : 0;
-    aside = std::max(aside, c);
+    for (const auto& cl : w.launches) c += cl.side ? 1 : 0;
+    aside = std::max(aside, w.mode == WAVE_MERGED ? 0 : w.mode == WAVE_SIDES_MERGED ? 1 : c);
   }
   for (; p.n_side < std::min(aside, Plan::kSide); ++p.n_side) {
     hipStream_t side = nullptr;
@@ -343,108 +342,87 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
     }
     return hipSuccess;
   };
-  // Every NS launch of one group (kernel class and form) of a wave, in order
-  // on one stream.
-  auto run_group = [&](const WaveHost& w, const ClassLaunch& cl, hipStream_t on) -> hipError_t {
-    auto gemm = [&](int32_t stage, int32_t kind, const GemmStep& g) {
-      const double fl = (kind == MUON_KERNEL_GRAM ? cl.flops_gram : kind == MUON_KERNEL_BX ? cl.flops_bx : cl.flops_poly) *
-                        (g.pair ? 2.0 : 1.0);
-      return run(kind, cl.kclass, fl, 0.0, on, [&] { return launch_ns_gemm(p, w, cl, stage, g, ws, s, on); });
-    };
-    hipError_t er = hipSuccess;
-    if (!cl.gram) {
-      // Eq. 2: per step A = s^2 X X^T, B = b A + c A A, X' = s (a X + B X),
-      // with step it's (a, b, c).  With c = 0 (a cubic step) the Gram stage
-      // writes B = b A itself.
-      for (int32_t it = 0; it < ns_steps && er == hipSuccess; ++it) {
-        const int32_t first = it == 0, pin = it & 1, last = it == ns_steps - 1;
-        const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
-        const bool cubic = c == 0.f;
-        er = gemm(ST_GRAM, MUON_KERNEL_GRAM,
-                  GemmStep{first, pin, last, SQ_A, SQ_A, cubic ? SQ_B : SQ_A, 0.f, 0.f, cubic ? b : 1.f});
-        if (er == hipSuccess && !cubic)
-          er = gemm(ST_POLY, MUON_KERNEL_POLY, GemmStep{first, pin, last, SQ_A, SQ_A, SQ_B, b / c, 0.f, c});
-        if (er == hipSuccess)
-          er = gemm(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, SQ_B, SQ_B, SQ_B, a, 0.f, 1.f});
-      }
-      return er;
+  OpList eq2_list, gram_list;
+  eq2_ops(p, ns_steps, eq2_list);
+  if (p.n_gram > 0) gram_ops(p, ns_steps, gram_list);
+  // Launch t of a group (kernel class and form) of a wave.
+  auto list_of = [&](const ClassLaunch& cl) -> const OpList& { return cl.gram ? gram_list : eq2_list; };
+  auto run_op = [&](const WaveHost& w, const ClassLaunch& cl, int t, hipStream_t on) -> hipError_t {
+    const GemmOp& op = list_of(cl).op[t];
+    const double fl = (op.kind == MUON_KERNEL_GRAM ? cl.flops_gram
+                       : op.kind == MUON_KERNEL_BX ? cl.flops_bx : cl.flops_poly) * (op.g.pair ? 2.0 : 1.0);
+    return run(op.kind, cl.kclass, fl, 0.0, on, [&] { return launch_ns_gemm(p, w, cl, op.stage, op.g, ws, s, on); });
+  };
+  // Launch t of the merged groups of a wave: the t-th product of each.
+  auto run_merged = [&](const WaveHost& w, int t, hipStream_t on) -> hipError_t {
+    const GemmOp* ops[kMaxParts] = {};
+    for (size_t i = 0; i < w.launches.size(); ++i) {
+      const ClassLaunch& cl = w.launches[i];
+      if (t < list_of(cl).n && (cl.side || w.mode == WAVE_MERGED)) ops[i] = &list_of(cl).op[t];
     }
-    // Gram space (Eq. 4), in segments of at most gram_restart steps.  A
-    // segment starting from X (X0 = s u in the first) forms G = X X^T; per
-    // step P_i = a_i I + b_i G + c_i G^2 (as c_i (G G + b_i/c_i G + a_i/c_i
-    // I); the plan takes this form only when no c_i is 0); Q_{i+1} = P_i Q_i
-    // (the segment's first P is written straight into Q0); R = G P_i and
-    // G <- P_i R except after the segment's last step; then X <- Q X, which
-    // after the last segment is O and goes into the update.  P Q and G P
-    // only need P_i, so they share one launch.  In segments of at most two
-    // steps R lives in B's memory and the second Q in A's (gram_shares_buffers):
-    // this order writes each only after the last read of what it replaces.
-    int32_t pin = 0;
-    for (int32_t s0 = 0; s0 < ns_steps && er == hipSuccess; s0 += p.gram_restart) {
-      const int32_t len = std::min(p.gram_restart, ns_steps - s0);
-      const int32_t first = s0 == 0, last = s0 + len == ns_steps;
-      er = gemm(ST_GRAM, MUON_KERNEL_GRAM, GemmStep{first, pin, 0, SQ_A, SQ_A, SQ_A, 0.f, 0.f, 1.f});
-      for (int32_t j = 0; j < len && er == hipSuccess; ++j) {
-        const int32_t it = s0 + j;
-        const int32_t pbuf = j == 0 ? SQ_Q0 : SQ_B;
-        const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
-        er = gemm(ST_POLY, MUON_KERNEL_POLY, GemmStep{0, 0, 0, SQ_A, SQ_A, pbuf, b / c, a / c, c});
-        const GemmStep qu{0, 0, 0, SQ_B, (j - 1) & 1 ? SQ_Q1 : SQ_Q0, j & 1 ? SQ_Q1 : SQ_Q0, 0.f, 0.f, 1.f};
-        GemmStep gr{0, 0, 0, SQ_A, pbuf, SQ_R, 0.f, 0.f, 1.f};
-        const bool need_qu = j > 0, need_gr = j + 1 < len;
-        if (er == hipSuccess && need_qu && need_gr) {
-          gr.pair = 1;
-          gr.l2 = qu.l;
-          gr.r2 = qu.r;
-          gr.out2 = qu.out;
-          er = gemm(ST_SYM, MUON_KERNEL_SYMM, gr);
-        } else if (er == hipSuccess && (need_qu || need_gr)) {
-          er = gemm(ST_SYM, MUON_KERNEL_SYMM, need_qu ? qu : gr);
-        }
-        if (er == hipSuccess && need_gr)
-          er = gemm(ST_SYM, MUON_KERNEL_SYMM, GemmStep{0, 0, 0, pbuf, SQ_R, SQ_A, 0.f, 0.f, 1.f});
-      }
-      const int32_t qk = (len - 1) & 1 ? SQ_Q1 : SQ_Q0;
-      if (er == hipSuccess)
-        er = gemm(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, qk, qk, qk, 0.f, 0.f, 1.f});
-      pin ^= 1;
-    }
-    return er;
+    if (!launch_merged(p, w, ops, ws, s, on)) return hipSuccess;
+    hipError_t er = hipGetLastError();
+    return er == hipSuccess ? hipErrorLaunchFailure : er;
   };
   // The groups of one wave.  Each is a chain of 15 or 17 dependent launches
   // (k = 5) that touches its own matrices only, so the chains run side by side:
   // one launch's last round, or a launch too small for the chip, then leaves
-  // no CU idle that another chain could use.  The group with the most work
-  // stays on the caller's stream; those that do not fill the chip for long
-  // (side_group) are enqueued first, on the plan's side streams, and joined
-  // back before the wave ends.  With launch
-  // timing on everything runs on the caller's stream, so that a launch's events
-  // time that launch alone.
+  // no CU idle that another chain could use (WaveMode; wave_mode in plan.cpp).
+  // The chains' launches are enqueued in turn, so that none of them waits for
+  // the host to have enqueued another to its end.  With launch timing on, every
+  // group runs its own launches on the caller's stream, so that a launch's
+  // events time that launch alone.
   auto run_groups = [&](const WaveHost& w) -> hipError_t {
     const int n = int(w.launches.size());
-    const int main_group = main_group_of(w);
-    auto aside = [&](int i) { return !timing && i != main_group && p.n_side > 0 && side_group(w.launches[size_t(i)]); };
-    bool any = false;
-    for (int i = 0; i < n; ++i) any = any || aside(i);
-    hipError_t er = any ? hipEventRecord(hipEvent_t(p.fork_event), hs) : hipSuccess;
-    int used = 0, next = 0;
-    for (int i = 0; i < n && er == hipSuccess; ++i) {
-      if (!aside(i)) continue;
-      hipStream_t on = hipStream_t(p.side[next]);
-      if (next >= used) {
-        er = hipStreamWaitEvent(on, hipEvent_t(p.fork_event), 0);
-        if (er != hipSuccess) break;
-        used = next + 1;
-      }
-      er = run_group(w, w.launches[size_t(i)], on);
-      next = (next + 1) % p.n_side;
+    hipError_t er = hipSuccess;
+    if (w.mode == WAVE_MERGED && !timing) {
+      const int len = std::max(eq2_list.n, gram_list.n);
+      for (int t = 0; t < len && er == hipSuccess; ++t) er = run_merged(w, t, hs);
+      return er;
     }
-    for (int i = 0; i < n && er == hipSuccess; ++i)
-      if (!aside(i)) er = run_group(w, w.launches[size_t(i)], hs);
+    auto aside = [&](const ClassLaunch& cl) { return cl.side && !timing && p.n_side > 0; };
+    // chain c < n_chains: stream and the groups that follow one another on it
+    int n_chains = 0, next = 0, chain_of[2 * KC_COUNT] = {}, at[Plan::kSide] = {}, pos[Plan::kSide] = {};
+    for (int i = 0; i < n; ++i) {
+      chain_of[i] = -1;  // the caller's stream
+      if (!aside(w.launches[size_t(i)])) continue;
+      if (w.mode == WAVE_SIDES_MERGED) {
+        n_chains = 1;
+        chain_of[i] = 0;
+      } else {
+        chain_of[i] = next;
+        n_chains = std::max(n_chains, next + 1);
+        next = (next + 1) % p.n_side;
+      }
+    }
+    if (n_chains > 0) er = hipEventRecord(hipEvent_t(p.fork_event), hs);
+    int forked = 0;
+    for (; forked < n_chains && er == hipSuccess; ++forked)
+      er = hipStreamWaitEvent(hipStream_t(p.side[forked]), hipEvent_t(p.fork_event), 0);
+    // the next launch of chain c (-1: the caller's stream); false when it has ended
+    auto advance = [&](int c, int& i, int& t) -> bool {
+      if (c >= 0 && w.mode == WAVE_SIDES_MERGED) {
+        if (t >= std::max(eq2_list.n, gram_list.n)) return false;
+        er = run_merged(w, t++, hipStream_t(p.side[c]));
+        return true;
+      }
+      while (i < n && (chain_of[i] != c || t >= list_of(w.launches[size_t(i)]).n)) {
+        ++i;
+        t = 0;
+      }
+      if (i >= n) return false;
+      er = run_op(w, w.launches[size_t(i)], t++, c < 0 ? hs : hipStream_t(p.side[c]));
+      return true;
+    };
+    int main_at = 0, main_pos = 0;
+    for (bool more = true; more && er == hipSuccess;) {
+      more = advance(-1, main_at, main_pos);
+      for (int c = 0; c < n_chains && er == hipSuccess; ++c) more = advance(c, at[c], pos[c]) || more;
+    }
     // joined on an error as well: nothing outlives the call's place in the stream
-    for (int k = 0; k < used; ++k) {
-      hipError_t ej = hipEventRecord(hipEvent_t(p.join_events[k]), hipStream_t(p.side[k]));
-      if (ej == hipSuccess) ej = hipStreamWaitEvent(hs, hipEvent_t(p.join_events[k]), 0);
+    for (int c = 0; c < forked; ++c) {
+      hipError_t ej = hipEventRecord(hipEvent_t(p.join_events[c]), hipStream_t(p.side[c]));
+      if (ej == hipSuccess) ej = hipStreamWaitEvent(hs, hipEvent_t(p.join_events[c]), 0);
       if (er == hipSuccess) er = ej;
     }
     return er;

@@ -143,7 +143,18 @@ struct ClassLaunch {
   // the lists above are the class's own tiles; a launch with too few of them
   // to fill the chip runs on smaller tiles instead (exec_tile in plan.cpp)
   StageRun run_gram, run_square, run_full;
+  bool side;                            // runs beside the wave's main group (side_group)
+  StageRun merged_lower, merged_full;   // 64-tile lists, where merged launches carry the group
 };
+
+// Most groups a merged launch can carry.
+constexpr int kMaxParts = 8;
+// How the groups of a wave, independent chains of launches, are run: the side
+// groups (ClassLaunch::side) on streams of their own beside the others; the
+// side groups together on one stream, a launch carrying the current product of
+// each on 64 tiles (merged_lower, merged_full); or all groups so, on the
+// caller's stream.
+enum WaveMode : int32_t { WAVE_APART = 0, WAVE_SIDES_MERGED = 1, WAVE_MERGED = 2 };
 
 struct WaveHost {
   int32_t first;       // first position in wave order
@@ -155,6 +166,7 @@ struct WaveHost {
   int64_t ws_bytes;
   double bytes_momentum, bytes_apply;  // algorithmic HBM bytes of one launch
   std::vector<ClassLaunch> launches;
+  int32_t mode;        // WaveMode
 };
 
 struct TimingRecord {
@@ -200,10 +212,9 @@ struct Plan {
   void* ring_events[kRing] = {};
   bool ring_busy[kRing] = {};
   int ring_next = 0;
-  // Side streams: the groups of a wave are independent between finalize and
-  // the end of the wave, so all but the largest run on streams of their own,
-  // forked from and joined to the caller's stream by events (run_groups in
-  // api.cpp).  Created with the plan, only as many as its waves can use.
+  // Side streams, for the side groups of a wave (WaveMode): forked from and
+  // joined to the caller's stream by events (run_groups in api.cpp).  Created
+  // with the plan, only as many as its waves can use.
   static constexpr int kSide = 3;
   int n_side = 0;
   void* side[kSide] = {};           // hipStream_t, default priority
@@ -254,6 +265,29 @@ inline int main_group_of(const WaveHost& w) {
   return best;
 }
 
+enum Stage : int32_t { ST_GRAM = 0, ST_POLY = 1, ST_BX = 2, ST_SYM = 3 };
+struct GemmStep {
+  int32_t first, pin, last;
+  int32_t l, r, out;          // SqBuf indices
+  float fcoef, diag, oscale;
+  int32_t pair = 0;           // ST_SYM: a second product over the same tiles
+  int32_t l2 = 0, r2 = 0, out2 = 0;
+};
+
+// The launches of one group for ns_steps NS steps, in order (plan.cpp).
+struct GemmOp {
+  int32_t stage, kind;       // Stage, muon_kernel_kind
+  GemmStep g;
+};
+struct OpList {
+  static constexpr int kMax = 4 * 64;   // at most 3 1/2 launches per step, max_ns_steps <= 64
+  int n = 0;
+  GemmOp op[kMax];
+  void add(int32_t stage, int32_t kind, const GemmStep& g) { op[n++] = GemmOp{stage, kind, g}; }
+};
+void eq2_ops(const Plan& p, int32_t ns_steps, OpList& out);
+void gram_ops(const Plan& p, int32_t ns_steps, OpList& out);
+
 // Per-launch arguments shared by the kernel launchers.
 struct StepScalars {
   float lr, mu, wd, decay;  // decay = 1 - lr*wd
@@ -282,15 +316,11 @@ int launch_apply(const Plan& p, const WaveHost& w, char* ws, const StepScalars& 
 // s is the Frobenius scale when `first` is set, else 1; `last` makes ST_BX
 // apply the update of Eq. 1 to the caller's parameters (and write O to the
 // debug buffer, if any) instead of writing x[pin ^ 1].
-enum Stage : int32_t { ST_GRAM = 0, ST_POLY = 1, ST_BX = 2, ST_SYM = 3 };
-struct GemmStep {
-  int32_t first, pin, last;
-  int32_t l, r, out;          // SqBuf indices
-  float fcoef, diag, oscale;
-  int32_t pair = 0;           // ST_SYM: a second product over the same tiles
-  int32_t l2 = 0, r2 = 0, out2 = 0;
-};
 int launch_ns_gemm(const Plan& p, const WaveHost& w, const ClassLaunch& cl, int32_t stage, const GemmStep& g,
                    char* ws, const StepScalars& s, void* stream);
+// One launch of a merged wave: op i is group i's current product (null: the
+// group has none left).
+int launch_merged(const Plan& p, const WaveHost& w, const GemmOp* const* ops, char* ws, const StepScalars& s,
+                  void* stream);
 
 }  // namespace muon

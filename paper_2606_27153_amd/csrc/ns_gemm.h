@@ -35,6 +35,19 @@ struct GemmArgs {
   float lr, decay;
 };
 
+// The parts of one launch that advances several groups of a wave at once.
+struct MultiPart {
+  const TileEntry* tiles;
+  GemmStep g;
+  int32_t stage, fp32, split;
+  int32_t end;   // first block of the next part
+};
+struct MultiArgs {
+  GemmArgs common;   // what the parts share (the wave's buffers, the update)
+  int32_t n;
+  MultiPart part[kMaxParts];
+};
+
 // Each launches `grid` blocks of its class's kernel for `stage` (Stage) on
 // st, the PAD instantiation of the 256 tile when `padded`, and returns 0,
 // or -1 when the launch failed.
@@ -46,6 +59,9 @@ int launch_t256_f16_sq(bool padded, int32_t stage, unsigned grid, const GemmArgs
 int launch_tile_bf16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
 int launch_tile_f16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
 int launch_tile_f32(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& g, hipStream_t st);
+// the parts' kernel, with bf16 or fp16 as the 16-bit operand type
+int launch_multi_bf16(unsigned grid, const MultiArgs& m, hipStream_t st);
+int launch_multi_f16(unsigned grid, const MultiArgs& m, hipStream_t st);
 
 }  // namespace muon
 

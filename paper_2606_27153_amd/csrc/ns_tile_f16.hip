@@ -13,4 +13,8 @@ int launch_tile_f16(int32_t exec, int32_t stage, unsigned grid, const GemmArgs& 
   }
 }
 
+int launch_multi_f16(unsigned grid, const MultiArgs& m, hipStream_t st) {
+  return launch_multi<_Float16>(grid, m, st);
+}
+
 }  // namespace muon

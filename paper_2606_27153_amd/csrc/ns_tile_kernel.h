@@ -24,15 +24,19 @@ __device__ __forceinline__ void wait_vm_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// LDS bytes of one slab of both operands, in any operand type.
+constexpr int tile_slab_bytes(int tile) { return 2 * tile * 128; }
+
+// Tile number `block` of one launch, in the NST * tile_slab_bytes(TILE) bytes
+// of LDS at lds.
 template <typename E, int TILE, int STAGE, int NST>
-__global__ __launch_bounds__(256) void ns_tile_kernel(GemmArgs args) {
+__device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* lds) {
   using C = Cfg<E, TILE, 2, 2>;
   constexpr bool TRB = STAGE == ST_BX && sizeof(E) == 2;
-  constexpr int STG = 2 * C::OPB;  // LDS bytes of one slab of both operands
-  __shared__ __attribute__((aligned(1024))) char lds[NST * STG];
+  constexpr int STG = tile_slab_bytes(TILE);
 
-  const bool second = STAGE == ST_SYM && int(blockIdx.x) >= args.split;
-  const TileEntry te = args.tiles[second ? int(blockIdx.x) - args.split : int(blockIdx.x)];
+  const bool second = STAGE == ST_SYM && block >= args.split;
+  const TileEntry te = args.tiles[second ? block - args.split : block];
   const int32_t bl = second ? args.l2 : args.l, br = second ? args.r2 : args.r, bo = second ? args.out2 : args.out;
   const MatDev& d = args.mats[te.mat];
   const int32_t slot = te.mat - args.mat_base;
@@ -237,6 +241,60 @@ __global__ __launch_bounds__(256) void ns_tile_kernel(GemmArgs args) {
     if (!TRB) store_t_via_lds<C, E>(acc, region, out_t, mp, row0, col0, lane);
     store_rows_via_lds<C, E>(acc, region, out_r, ld_r, row0, col0, lane);
   }
+}
+
+template <typename E, int TILE, int STAGE, int NST>
+__global__ __launch_bounds__(256) void ns_tile_kernel(GemmArgs args) {
+  __shared__ __attribute__((aligned(1024))) char lds[NST * tile_slab_bytes(TILE)];
+  run_tile<E, TILE, STAGE, NST>(args, int(blockIdx.x), lds);
+}
+
+// One launch that carries the current product of several groups of a wave,
+// whatever their stage and operand type (16-bit E or fp32), all on 64 tiles.
+// Block b belongs to the first part whose `end` exceeds it.
+template <typename E>
+__global__ __launch_bounds__(256) void ns_multi_kernel(MultiArgs m) {
+  __shared__ __attribute__((aligned(1024))) char lds[3 * tile_slab_bytes(64)];
+  const int b = int(blockIdx.x);
+  int i = 0, begin = 0;
+  while (i + 1 < m.n && b >= m.part[i].end) begin = m.part[i++].end;
+  const MultiPart& q = m.part[i];
+  GemmArgs a = m.common;
+  a.tiles = q.tiles;
+  a.fcoef = q.g.fcoef;
+  a.diag = q.g.diag;
+  a.oscale = q.g.oscale;
+  a.first = q.g.first;
+  a.pin = q.g.pin;
+  a.last = q.g.last;
+  a.l = q.g.l;
+  a.r = q.g.r;
+  a.out = q.g.out;
+  a.l2 = q.g.l2;
+  a.r2 = q.g.r2;
+  a.out2 = q.g.out2;
+  a.split = q.split;
+  const int t = b - begin;
+  if (q.fp32) {
+    switch (q.stage) {
+      case ST_GRAM: run_tile<float, 64, ST_GRAM, 3>(a, t, lds); break;
+      case ST_POLY: run_tile<float, 64, ST_POLY, 3>(a, t, lds); break;
+      default: run_tile<float, 64, ST_BX, 3>(a, t, lds); break;
+    }
+  } else {
+    switch (q.stage) {
+      case ST_GRAM: run_tile<E, 64, ST_GRAM, 3>(a, t, lds); break;
+      case ST_POLY: run_tile<E, 64, ST_POLY, 3>(a, t, lds); break;
+      case ST_SYM: run_tile<E, 64, ST_SYM, 3>(a, t, lds); break;
+      default: run_tile<E, 64, ST_BX, 3>(a, t, lds); break;
+    }
+  }
+}
+
+template <typename E>
+int launch_multi(unsigned nblocks, const MultiArgs& m, hipStream_t st) {
+  hipLaunchKernelGGL(ns_multi_kernel<E>, dim3(nblocks), dim3(256), 0, st, m);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Any stage of one class.

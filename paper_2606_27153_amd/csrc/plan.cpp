@@ -202,6 +202,7 @@ constexpr int64_t kExecMaxTiles = 4 * kCus;
 struct TileLoad {
   int64_t m_pad, n_pad;   // n_pad = 0: a symmetric output (lower tiles)
   int64_t slabs;
+  bool fp32;
 };
 
 int64_t tile_count(const TileLoad& t, int64_t tile) {
@@ -209,22 +210,36 @@ int64_t tile_count(const TileLoad& t, int64_t tile) {
   return t.n_pad ? a * b : a * (a + 1) / 2;
 }
 
-// Estimated time of a launch over these matrices on one kernel.
-double exec_time(const std::vector<TileLoad>& loads, const ExecModel& e) {
-  int64_t total = 0;
-  for (const TileLoad& t : loads) total += tile_count(t, e.tile);
-  const double share = e.occ == 1 ? double(std::min(total, kCus)) / double(kCus)
-                                  : double(std::min(std::max<int64_t>(total - kCus, 0), kCus * (e.occ - 1))) /
+// Time of one slab of a tile when `tiles` of them share the chip.
+double slab_time(const ExecModel& e, int64_t tiles) {
+  const double share = e.occ == 1 ? double(std::min(tiles, kCus)) / double(kCus)
+                                  : double(std::min(std::max<int64_t>(tiles - kCus, 0), kCus * (e.occ - 1))) /
                                         double(kCus * (e.occ - 1));
-  const double slab = e.alone + (e.full - e.alone) * share;
-  const int64_t slots = std::min(total, kCus * e.occ);
+  return e.alone + (e.full - e.alone) * share;
+}
+
+// Estimated time of a launch over these matrices on one kernel.
+double exec_time(const std::vector<TileLoad>& loads, int32_t exec) {
+  int64_t total = 0, total32 = 0;
+  for (const TileLoad& t : loads) {
+    const int64_t n = tile_count(t, (t.fp32 ? kExec32 : kExec16)[exec].tile);
+    total += n;
+    total32 += t.fp32 ? n : 0;
+  }
+  if (total == 0) return 0.0;
+  // fp32 tiles compete for the matrix cores with each other, 16-bit tiles for
+  // LDS and L2 with all
+  const double slab16 = slab_time(kExec16[exec], total), slab32 = slab_time(kExec32[exec], total32);
+  const ExecModel& any = kExec16[exec];
+  const int64_t slots = std::min(total, kCus * any.occ);
   std::vector<double> heap(size_t(slots), 0.0);  // min-heap of slot end times
   double end = 0;
   for (size_t i = 0; i < loads.size();) {
     const int64_t slabs = loads[i].slabs;
-    const double dt = e.over + double(slabs) * slab;
+    const bool fp32 = loads[i].fp32;
+    const double dt = any.over + double(slabs) * (fp32 ? slab32 : slab16);
     int64_t n = 0;  // tiles of a run of matrices with the same K
-    for (; i < loads.size() && loads[i].slabs == slabs; ++i) n += tile_count(loads[i], e.tile);
+    for (; i < loads.size() && loads[i].slabs == slabs && loads[i].fp32 == fp32; ++i) n += tile_count(loads[i], any.tile);
     // all but the last two rounds of a long run level out over the slots
     if (n > 2 * slots) {
       const int64_t rounds = n / slots - 1;
@@ -238,30 +253,161 @@ double exec_time(const std::vector<TileLoad>& loads, const ExecModel& e) {
       std::push_heap(heap.begin(), heap.end(), std::greater<double>());
     }
   }
-  return e.start + end;
+  return any.start + end;
 }
 
 // The kernel for a launch whose class tile is `tile` and whose class lists
-// hold `class_tiles` tiles.
-int32_t exec_tile(const std::vector<TileLoad>& loads, int32_t tile, bool fp32, int64_t class_tiles) {
+// hold `class_tiles` tiles; *us receives its estimated time.
+int32_t exec_tile(const std::vector<TileLoad>& loads, int32_t tile, bool fp32, int64_t class_tiles, double* us) {
   int32_t best = tile == 256 ? EX_256 : tile == 128 ? EX_128_RING2 : EX_64_RING3;
+  *us = 0;
   if (class_tiles > kExecMaxTiles) return best;
-  double best_t = 0;
   for (int32_t x = 0; x < EX_COUNT; ++x) {
     const ExecModel& e = fp32 ? kExec32[x] : kExec16[x];
     if (e.tile == 0 || e.tile > tile) continue;
-    const double t = exec_time(loads, e);
-    if (best_t == 0 || t < best_t) {
+    const double t = exec_time(loads, x);
+    if (*us == 0 || t < *us) {
       best = x;
-      best_t = t;
+      *us = t;
     }
   }
   return best;
 }
 
+// The launches of one group by kind, for the choice between a chain of its own
+// and a merged wave.
+struct GroupLoads {
+  std::vector<TileLoad> gram, square, full;
+  double us_gram, us_square, us_full;   // a launch on the group's own kernels (0: not estimated)
+  const std::vector<TileLoad>& of(int32_t stage) const {
+    return stage == ST_GRAM ? gram : stage == ST_BX ? full : square;
+  }
+  double us(int32_t stage) const { return stage == ST_GRAM ? us_gram : stage == ST_BX ? us_full : us_square; }
+};
+
+// How a wave's groups are launched (WaveMode).  A launch costs the host
+// 3.2 to 4 us, and forking a chain off and joining it about 12 us of the GPU's time,
+// so small groups are bound by the number of launches: the tiny set has 32 in
+// two chains and 17 merged.  Merging gives up the larger tiles and makes every
+// product wait for the longest of its launch; the mode with the shortest
+// estimated time is taken.
+int32_t wave_mode(const Plan& p, const WaveHost& w, const std::vector<GroupLoads>& groups) {
+  constexpr double kHostUs = 4.0, kForkUs = 12.0;
+  const size_t n = groups.size();
+  if (n < 2 || n > size_t(kMaxParts)) return WAVE_APART;
+  OpList list[2];
+  const int32_t k = std::min(p.opts.max_ns_steps, 5);
+  eq2_ops(p, k, list[0]);
+  if (p.n_gram > 0) gram_ops(p, k, list[1]);
+  double in_line = 0, longest = 0, launches = 0, line_launches = 0;
+  int32_t len = 0, side_len = 0, sides = 0;
+  std::vector<char> side(n, 0);
+  for (size_t i = 0; i < n; ++i) {
+    const OpList& o = list[w.launches[i].gram];
+    side[i] = int(i) != main_group_of(w) && side_group(w.launches[i]);
+    double chain = 0;
+    for (int32_t t = 0; t < o.n; ++t) chain += groups[i].us(o.op[t].stage);
+    len = std::max(len, o.n);
+    launches += o.n;
+    if (side[i]) {
+      if (chain == 0) return WAVE_APART;
+      longest = std::max(longest, chain);
+      side_len = std::max(side_len, o.n);
+      ++sides;
+    } else {
+      // a group too large to be estimated fills the chip: its chain is the wave
+      if (chain == 0) return WAVE_APART;
+      in_line += chain;
+      line_launches += o.n;
+    }
+  }
+  auto merged_us = [&](bool sides_only) {
+    double us = 0;
+    for (int32_t t = 0; t < (sides_only ? side_len : len); ++t) {
+      std::vector<TileLoad> all;
+      for (size_t i = 0; i < n; ++i) {
+        const OpList& o = list[w.launches[i].gram];
+        if (t >= o.n || (sides_only && !side[i])) continue;
+        const std::vector<TileLoad>& l = groups[i].of(o.op[t].stage);
+        all.insert(all.end(), l.begin(), l.end());
+      }
+      us += exec_time(all, EX_64_RING3);
+    }
+    return us;
+  };
+  const double fork = sides ? kForkUs : 0.0;
+  double best = std::max(std::max(in_line, longest) + fork, launches * kHostUs);
+  int32_t mode = WAVE_APART;
+  if (sides > 1) {
+    const double t = std::max(std::max(in_line, merged_us(true)) + fork, (line_launches + side_len) * kHostUs);
+    if (t < best) {
+      best = t;
+      mode = WAVE_SIDES_MERGED;
+    }
+  }
+  if (std::max(merged_us(false), len * kHostUs) < best) mode = WAVE_MERGED;
+  return mode;
+}
+
 }  // namespace
 
 const ClassInfo& class_info(int32_t kc) { return kClasses[kc]; }
+
+// Eq. 2: per step A = s^2 X X^T, B = b A + c A A, X' = s (a X + B X), with step
+// it's (a, b, c).  With c = 0 (a cubic step) the Gram stage writes B = b A
+// itself.
+void eq2_ops(const Plan& p, int32_t ns_steps, OpList& out) {
+  for (int32_t it = 0; it < ns_steps; ++it) {
+    const int32_t first = it == 0, pin = it & 1, last = it == ns_steps - 1;
+    const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
+    const bool cubic = c == 0.f;
+    out.add(ST_GRAM, MUON_KERNEL_GRAM,
+            GemmStep{first, pin, last, SQ_A, SQ_A, cubic ? SQ_B : SQ_A, 0.f, 0.f, cubic ? b : 1.f});
+    if (!cubic) out.add(ST_POLY, MUON_KERNEL_POLY, GemmStep{first, pin, last, SQ_A, SQ_A, SQ_B, b / c, 0.f, c});
+    out.add(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, SQ_B, SQ_B, SQ_B, a, 0.f, 1.f});
+  }
+}
+
+// Gram space (Eq. 4), in segments of at most gram_restart steps.  A segment
+// starting from X (X0 = s u in the first) forms G = X X^T; per step P_i = a_i I
+// + b_i G + c_i G^2 (as c_i (G G + b_i/c_i G + a_i/c_i I); the plan takes this
+// form only when no c_i is 0); Q_{i+1} = P_i Q_i (the segment's first P is
+// written straight into Q0); R = G P_i and G <- P_i R except after the
+// segment's last step; then X <- Q X, which after the last segment is O and
+// goes into the update.  P Q and G P only need P_i, so they share one launch.
+// In segments of at most two steps R lives in B's memory and the second Q in
+// A's (gram_shares_buffers): this order writes each only after the last read
+// of what it replaces.
+void gram_ops(const Plan& p, int32_t ns_steps, OpList& out) {
+  int32_t pin = 0;
+  for (int32_t s0 = 0; s0 < ns_steps; s0 += p.gram_restart) {
+    const int32_t len = std::min(p.gram_restart, ns_steps - s0);
+    const int32_t first = s0 == 0, last = s0 + len == ns_steps;
+    out.add(ST_GRAM, MUON_KERNEL_GRAM, GemmStep{first, pin, 0, SQ_A, SQ_A, SQ_A, 0.f, 0.f, 1.f});
+    for (int32_t j = 0; j < len; ++j) {
+      const int32_t it = s0 + j;
+      const int32_t pbuf = j == 0 ? SQ_Q0 : SQ_B;
+      const float a = p.abc[size_t(3 * it)], b = p.abc[size_t(3 * it + 1)], c = p.abc[size_t(3 * it + 2)];
+      out.add(ST_POLY, MUON_KERNEL_POLY, GemmStep{0, 0, 0, SQ_A, SQ_A, pbuf, b / c, a / c, c});
+      const GemmStep qu{0, 0, 0, SQ_B, (j - 1) & 1 ? SQ_Q1 : SQ_Q0, j & 1 ? SQ_Q1 : SQ_Q0, 0.f, 0.f, 1.f};
+      GemmStep gr{0, 0, 0, SQ_A, pbuf, SQ_R, 0.f, 0.f, 1.f};
+      const bool need_qu = j > 0, need_gr = j + 1 < len;
+      if (need_qu && need_gr) {
+        gr.pair = 1;
+        gr.l2 = qu.l;
+        gr.r2 = qu.r;
+        gr.out2 = qu.out;
+        out.add(ST_SYM, MUON_KERNEL_SYMM, gr);
+      } else if (need_qu || need_gr) {
+        out.add(ST_SYM, MUON_KERNEL_SYMM, need_qu ? qu : gr);
+      }
+      if (need_gr) out.add(ST_SYM, MUON_KERNEL_SYMM, GemmStep{0, 0, 0, pbuf, SQ_R, SQ_A, 0.f, 0.f, 1.f});
+    }
+    const int32_t qk = (len - 1) & 1 ? SQ_Q1 : SQ_Q0;
+    out.add(ST_BX, MUON_KERNEL_BX, GemmStep{first, pin, last, qk, qk, qk, 0.f, 0.f, 1.f});
+    pin ^= 1;
+  }
+}
 
 int64_t launches_per_step(const Plan& p, int32_t ns_steps) {
   // Per (class, form) group, lower-tile stages and B*X stages.  Eq. 2: Gram,
@@ -510,6 +656,34 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
     w.ws_bytes = off;
     p.ws_bytes = std::max(p.ws_bytes, off);
 
+    std::vector<GroupLoads> groups;                                        // as w.launches
+    std::map<std::tuple<int32_t, int64_t, bool>, StageRun> lists;          // (class and form, tile, full)
+    // group cl's lists on kernel `exec`: its own, or smaller tiles (made once)
+    auto small_run = [&](const WaveHost& wv, const ClassLaunch& cl, int32_t exec, bool is_full) {
+      const int64_t t = kExec16[exec].tile;
+      StageRun r{exec, is_full ? cl.full_off : cl.lower_off, is_full ? cl.n_full : cl.n_lower};
+      if (t == kClasses[cl.kclass].tile) return r;
+      StageRun& list = lists[std::make_tuple(cl.kclass * 2 + cl.gram, t, is_full)];
+      if (list.n == 0) {
+        std::vector<std::vector<TileEntry>> u;
+        std::vector<TileEntry> out;
+        for (int32_t s = 0; s < wv.count; ++s) {
+          const MatHost& h = p.mats[size_t(p.order[size_t(wv.first + s)])];
+          if (h.kclass != cl.kclass || h.gram != cl.gram) continue;
+          if (is_full)
+            full_units(u, wv.first + s, h.m_pad / t, h.n_pad / t);
+          else
+            lower_units(u, wv.first + s, h.m_pad / t);
+        }
+        interleave_units(out, u);
+        list.off = int64_t(p.h_tiles.size());
+        list.n = int32_t(out.size());
+        p.h_tiles.insert(p.h_tiles.end(), out.begin(), out.end());
+      }
+      r.off = list.off;
+      r.n = list.n;
+      return r;
+    };
     for (int32_t kg = 0; kg < 2 * KC_COUNT; ++kg) {
       const int32_t kc = kg / 2, gram = kg % 2;
       std::vector<TileEntry> lower, full, strip_full;
@@ -582,48 +756,36 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
       cl.n_strip_full = int32_t(strip_full.size());
       p.h_tiles.insert(p.h_tiles.end(), strip_full.begin(), strip_full.end());
       // the tiles each kind of launch runs on
-      std::vector<TileLoad> lg, ls, lf;
+      GroupLoads gl{};
       for (int32_t s = 0; s < w.count; ++s) {
         const MatHost& h = p.mats[size_t(p.order[size_t(w.first + s)])];
         if (h.kclass != kc || h.gram != gram) continue;
-        const int64_t bk = kClasses[kc].fp32 ? 32 : 64;
+        const bool f32 = kClasses[kc].fp32 != 0;
+        const int64_t bk = f32 ? 32 : 64;
         const int64_t sm = (h.m + bk - 1) / bk, sn = (h.n + bk - 1) / bk;
-        lg.push_back(TileLoad{h.m_pad, 0, sn});
-        ls.push_back(TileLoad{h.m_pad, 0, sm});
-        lf.push_back(TileLoad{h.m_pad, h.n_pad, sm});
+        gl.gram.push_back(TileLoad{h.m_pad, 0, sn, f32});
+        gl.square.push_back(TileLoad{h.m_pad, 0, sm, f32});
+        gl.full.push_back(TileLoad{h.m_pad, h.n_pad, sm, f32});
       }
-      std::map<std::pair<int64_t, bool>, StageRun> small;  // (tile, full) -> list built so far
-      auto stage_run = [&](const std::vector<TileLoad>& loads, bool is_full) {
+      auto stage_run = [&](const std::vector<TileLoad>& loads, bool is_full, double* us) {
         const int64_t own = is_full ? cl.n_full + cl.n_strip_full : cl.n_lower;
-        StageRun r{exec_tile(loads, int32_t(tile), kClasses[kc].fp32 != 0, own), is_full ? cl.full_off : cl.lower_off,
-                   is_full ? cl.n_full : cl.n_lower};
-        const int64_t t = kExec16[r.exec].tile;
-        if (t == tile) return r;
-        StageRun& list = small[{t, is_full}];
-        if (list.n == 0) {
-          std::vector<std::vector<TileEntry>> u;
-          std::vector<TileEntry> out;
-          for (int32_t s = 0; s < w.count; ++s) {
-            const MatHost& h = p.mats[size_t(p.order[size_t(w.first + s)])];
-            if (h.kclass != kc || h.gram != gram) continue;
-            if (is_full)
-              full_units(u, w.first + s, h.m_pad / t, h.n_pad / t);
-            else
-              lower_units(u, w.first + s, h.m_pad / t);
-          }
-          interleave_units(out, u);
-          list.off = int64_t(p.h_tiles.size());
-          list.n = int32_t(out.size());
-          p.h_tiles.insert(p.h_tiles.end(), out.begin(), out.end());
-        }
-        r.off = list.off;
-        r.n = list.n;
-        return r;
+        const int32_t exec = exec_tile(loads, int32_t(tile), kClasses[kc].fp32 != 0, own, us);
+        return small_run(w, cl, exec, is_full);
       };
-      cl.run_gram = stage_run(lg, false);
-      cl.run_square = stage_run(ls, false);
-      cl.run_full = stage_run(lf, true);
+      cl.run_gram = stage_run(gl.gram, false, &gl.us_gram);
+      cl.run_square = stage_run(gl.square, false, &gl.us_square);
+      cl.run_full = stage_run(gl.full, true, &gl.us_full);
+      groups.push_back(std::move(gl));
       w.launches.push_back(cl);
+    }
+    w.mode = wave_mode(p, w, groups);
+    for (int32_t i = 0; i < int32_t(w.launches.size()); ++i) {
+      ClassLaunch& cl = w.launches[size_t(i)];
+      cl.side = i != main_group_of(w) && side_group(cl);
+      if (w.mode == WAVE_MERGED || (w.mode == WAVE_SIDES_MERGED && cl.side)) {
+        cl.merged_lower = small_run(w, cl, EX_64_RING3, false);
+        cl.merged_full = small_run(w, cl, EX_64_RING3, true);
+      }
     }
   }
   p.h_ptrs.assign(size_t(n), PtrEntry{nullptr, nullptr, nullptr, nullptr});

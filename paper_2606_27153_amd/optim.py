@@ -43,6 +43,7 @@ def check_step_tensors(descs: Sequence, params: List, grads: List, moms: List, w
     A grad may be None (the matrix is skipped for the step).  ``only``
     restricts the per-matrix checks to those indices.  The library itself
     only sees pointers and cannot tell."""
+    import torch
     n = len(descs)
     if not (len(params) == len(grads) == len(moms) == n):
         raise ValueError(f"expected {n} params, grads and momentum buffers")
@@ -64,7 +65,8 @@ def check_step_tensors(descs: Sequence, params: List, grads: List, moms: List, w
             what = f"matrix {i} {name}"
             if tuple(t.shape) != shape:
                 raise ValueError(f"{what} has shape {tuple(t.shape)}, the plan expects {shape}")
-            if _dtype_code(t) != code:
+            if t.dtype != (torch.float32 if code == L.MUON_F32 else torch.bfloat16):
+                _dtype_code(t)   # a dtype the library lacks is a TypeError
                 raise ValueError(f"{what} has dtype {t.dtype}, the plan expects "
                                  f"{'float32' if code == L.MUON_F32 else 'bfloat16'}")
             if not t.is_contiguous():
@@ -169,6 +171,7 @@ class MuonPlan:
         self.precision = precision
         self._workspace = None
         self._checked = None     # buffer addresses of the last checked call
+        self._arrays = (None,) * 4   # the same as C arrays
 
     # ------------------------------------------------------------ inspection
     @property
@@ -254,20 +257,29 @@ class MuonPlan:
         last = self._checked
         if last is None or last[4] != wsp or (last[3] is None) != (op is None):
             todo = None   # everything
+        elif pp == last[0] and gp == last[1] and mp == last[2] and op == last[3]:
+            todo = []
         else:
             todo = [i for i in range(n) if pp[i] != last[0][i] or gp[i] != last[1][i] or mp[i] != last[2][i]
                     or (op is not None and op[i] != last[3][i])]
         if todo is None or todo:
             check_step_tensors(self.descs, params, grads, moms, workspace, update_out, only=todo)
-        self._checked = (pp, gp, mp, op, wsp)
-        args = (self._h, L.ptr_array(pp), L.ptr_array(gp), L.ptr_array(mp), float(lr), float(momentum),
-                float(weight_decay), int(ns_steps), 1 if nesterov else 0, ctypes.c_void_p(wsp),
-                workspace.numel() * workspace.element_size(), ctypes.c_void_p(sp))
+            # the C arrays of one address list are kept while the list stays
+            # the same (filling them costs about as much as the rest of the call)
+            old = self._arrays if last is not None else (None,) * 4
+            self._arrays = tuple(
+                None if new is None else arr if last is not None and arr is not None and new == last[k]
+                else L.ptr_array(new) for k, (new, arr) in enumerate(zip((pp, gp, mp, op), old)))
+            self._checked = (pp, gp, mp, op, wsp)
+        pa, ga, ma, oa = self._arrays
+        args = (self._h, pa, ga, ma, float(lr), float(momentum), float(weight_decay), int(ns_steps),
+                1 if nesterov else 0, ctypes.c_void_p(wsp), workspace.numel() * workspace.element_size(),
+                ctypes.c_void_p(sp))
         lib = L.load()
         if update_out is None:
             L.check(lib.muon_step(*args))
         else:
-            L.check(lib.muon_step_debug(*args, L.ptr_array(op)))
+            L.check(lib.muon_step_debug(*args, oa))
 
     def close(self) -> None:
         if getattr(self, "_h", None) is not None and self._h.value:

@@ -4,8 +4,8 @@
 // and kind of launch, the run's list must cover the group's padded outputs
 // exactly once (lower tiles: every cell on or below the diagonal, directly or
 // inside a diagonal tile) with a tile that divides the padding, and large
-// groups must keep their class tiles.  Arguments: precision.  Prints "OK" and
-// how many runs use each kernel.
+// groups must keep their class tiles.  Arguments: precision.  Prints "OK", how
+// many runs use each kernel, and how many waves have each mode.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -38,14 +38,21 @@ int main(int argc, char** argv) {
   std::string err;
   if (build_plan(descs.data(), int32_t(descs.size()), o, p, err) != MUON_OK) return fail("build_plan: " + err);
   static const int kTile[EX_COUNT] = {256, 128, 128, 64};
-  int used[EX_COUNT] = {};
+  int used[EX_COUNT] = {}, modes[3] = {};
   for (const WaveHost& w : p.waves)
     for (const ClassLaunch& cl : w.launches) {
       const ClassInfo& ci = class_info(cl.kclass);
-      const StageRun runs[3] = {cl.run_gram, cl.run_square, cl.run_full};
-      for (int kind = 0; kind < 3; ++kind) {
+      // a merged wave runs on its groups' 64-tile lists (the others serve
+      // launch timing)
+      const StageRun runs[5] = {cl.run_gram, cl.run_square, cl.run_full, cl.merged_lower, cl.merged_full};
+      if (w.mode != WAVE_APART && (w.launches.size() < 2 || w.launches.size() > size_t(kMaxParts)))
+        return fail("merged groups");
+      modes[w.mode] += &cl == &w.launches[0];
+      const bool carried = w.mode == WAVE_MERGED || (w.mode == WAVE_SIDES_MERGED && cl.side);
+      for (int kind = 0; kind < (carried ? 5 : 3); ++kind) {
         const StageRun& run = runs[kind];
-        const bool full = kind == 2;
+        const bool full = kind == 2 || kind == 4;
+        if (kind > 2 && run.exec != EX_64_RING3) return fail("merged tile");
         const int t = kTile[run.exec];
         used[run.exec]++;
         if (t > ci.tile) return fail("tile larger than the class's");
@@ -84,6 +91,7 @@ int main(int argc, char** argv) {
         }
       }
     }
-  std::printf("OK %d %d %d %d\n", used[0], used[1], used[2], used[3]);
+  std::printf("OK %d %d %d %d %d %d %d\n", used[0], used[1], used[2], used[3], modes[0], modes[1],
+              modes[2]);
   return 0;
 }

@@ -1,6 +1,7 @@
 """Launches that would leave much of the chip idle run on smaller tiles than
 their class's.  Host: the lists they run on cover every output exactly once.
-GPU: an element's value does not depend on the tile that computed it -- a
+GPU: an element's value does not depend on the tile that computed it, nor on
+what it was launched with -- a
 matrix on its own (small tiles) and the same matrix among enough others to
 fill the chip (256 tiles with their half tiles and edge strips, or the class
 tile) give bitwise the same W, M and O."""
@@ -36,7 +37,7 @@ def _run(exe, shapes, precision):
 @pytest.mark.parametrize("precision", [0, 1, 2])
 def test_lists_cover_outputs(lists_check, precision):
     rng = np.random.default_rng(7)
-    used = np.zeros(4, int)
+    used = np.zeros(7, int)
     for n in (1, 2, 3, 5, 9, 17):
         for _ in range(6):
             shapes = [(int(rng.integers(1, 2600)), int(rng.integers(1, 2600))) for _ in range(n)]
@@ -45,6 +46,13 @@ def test_lists_cover_outputs(lists_check, precision):
         used += _run(lists_check, [(r, c)], precision)
     # every kernel the precision has is chosen somewhere
     assert used[1] and used[3] and (precision == 1 or (used[0] and used[2])), used
+    # the tiny set's two groups advance together, the 8B set's do not
+    if precision == 0:
+        ragged = [(65, 200), (200, 65), (130, 700), (700, 130), (257, 513), (513, 257), (1000, 1000), (96, 4304),
+                  (7, 13), (1152, 1200), (300, 300)]
+        assert _run(lists_check, ragged, 0)[4:] == [0, 1, 0]   # its side groups share launches
+        tiny, big = (_run(lists_check, [(m.rows, m.cols) for m in get_workload(k).matrices], 0) for k in ("tiny", "8b"))
+        assert tiny[4:] == [0, 0, 1] and big[5:] == [0, 0]
     for key in WORKLOAD_KEYS:
         _run(lists_check, [(m.rows, m.cols) for m in get_workload(key).matrices], precision)
 
@@ -75,3 +83,63 @@ def test_value_does_not_depend_on_the_tile(shape, many, precision):
     for a, b in zip(*got):
         assert torch.isfinite(a).all()
         assert torch.equal(a, b)
+
+
+# waves of small groups of every kind (Eq. 2 and Gram space on the 256, 128 and
+# 64 classes, fp32 for small m under bf16; odd columns, tall matrices): all
+# merged, side groups sharing launches beside a main group, side groups on
+# streams of their own beside a large one
+SMALL = [(256, 768), (768, 256), (300, 301), (130, 700), (96, 520), (70, 72), (40, 200), (200, 33), (64, 64), (512, 512)]
+WAVES = {"merged": SMALL,
+         "sides merged": [(257, 513), (513, 257), (130, 700), (96, 4304), (1000, 1000), (7, 13), (1152, 1200), (300, 300),
+                          (65, 200)],
+         "side streams": SMALL + [(1024, 1024)] * 40}
+
+
+def test_wave_modes(lists_check):
+    assert [_run(lists_check, WAVES[k], 0)[4:] for k in WAVES] == [[0, 0, 1], [0, 1, 0], [1, 0, 0]]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["bf16", "fp16"])
+@pytest.mark.parametrize("wave", list(WAVES))
+def test_groups_run_together_match_each_matrix_alone(wave, precision):
+    # several steps, one matrix with a zero gradient, one without a gradient:
+    # bitwise each matrix on its own; then the same step captured in a graph and
+    # replayed between eager steps
+    dev = "cuda:0"
+    wl = custom_workload(WAVES[wave], seed=73)
+    kw = dict(lr=0.02, momentum=0.95, weight_decay=0.01, ns_steps=5)
+    descs = [(m.rows, m.cols, m.param, m.grad) for m in wl.matrices]
+    plan = MuonPlan(descs, precision=precision)
+    params, moms = make_state(torch, wl, dev)
+    alone = [(p.clone(), m.clone()) for p, m in zip(params, moms)]
+    plans = [MuonPlan([d], precision=precision) for d in descs[:10]]
+
+    def check(grads, what):
+        for i, q in enumerate(plans):
+            q.step([alone[i][0]], [grads[i]], [alone[i][1]], **kw)
+        torch.cuda.synchronize()
+        for i in range(len(plans)):
+            assert torch.equal(params[i], alone[i][0]) and torch.equal(moms[i], alone[i][1]), (descs[i], what)
+
+    for step in range(2):
+        grads = make_grads(torch, wl, step, dev)
+        grads[2].zero_()
+        grads[3] = None if step else grads[3]
+        plan.step(params, grads, moms, **kw)
+        check(grads, f"step {step}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.step(params, grads, moms, **kw)
+    for replay in range(4):
+        for g, new in zip(grads, make_grads(torch, wl, 2 + replay, dev)):
+            if g is not None:
+                g.copy_(new)
+        if replay == 2:
+            plan.step(params, grads, moms, **kw)
+            check(grads, "eager between replays")
+        graph.replay()
+        check(grads, f"replay {replay}")
+    for q in plans + [plan]:
+        q.close()
