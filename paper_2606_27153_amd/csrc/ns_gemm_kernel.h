@@ -396,6 +396,90 @@ __device__ __forceinline__ void store_t_via_lds(const f32x16 (&acc)[C::NBM][C::N
   }
 }
 
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef short i16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ i16x4 lds_tr16(const char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(p));
+}
+
+// Epilogue stores of the 256 tile's wave pieces (128 x 64, 16-bit).  The piece
+// goes to LDS once, in a transposed layout: LDS row j (256 bytes) holds the 128
+// values of column j, so a lane's 4 consecutive-row accumulator values are one
+// 8-byte write.  16-byte pieces are XOR-swizzled with col_swz(j): the 16 values
+// it takes over 16 consecutive rows keep the writes spread over the banks, and
+// 4 consecutive rows get 4 different pairs of pieces, which the transposing
+// reads below need to be free of conflicts.
+//   TRANS: out_t[(col0 + j) * ld_t + row0 + i], whole LDS rows.
+//   ROWS:  out_r[(row0 + i) * ld_r + col0 + j]: ds_read_b64_tr_b16 hands each
+//          lane 4 + 4 consecutive columns of one row; these go back to the
+//          region row by row, from which whole lines are stored.
+// The row-major copy used to be staged on its own with 128 2-byte LDS writes per
+// lane; now it takes 32 transposing reads and 16 16-byte writes.  (Stored straight
+// from the transposing reads, in half lines of 64 bytes, the MoE experts' step took
+// 17.3 ms instead of 16.9; the old staging 17.05.)
+// MASK: only the 32 x 32 blocks (i, j) with bit i * NBN + j of tmask / rmask set.
+__device__ __forceinline__ int col_swz(int j) { return ((j & 7) << 1) | ((j >> 3) & 1); }
+
+template <class C, typename OUT, bool TRANS, bool ROWS, bool MASK>
+__device__ __forceinline__ void store_piece16(const f32x16 (&acc)[C::NBM][C::NBN], char* region, OUT* out_t,
+                                              int64_t ld_t, OUT* out_r, int64_t ld_r, int64_t row0, int64_t col0,
+                                              int lane, uint32_t tmask = 0, uint32_t rmask = 0) {
+  static_assert(sizeof(OUT) == 2 && C::WTM == 128 && C::WTN * 256 <= C::WAVE_LDS, "one pass holds the piece");
+#pragma unroll
+  for (int j = 0; j < C::NBN; ++j) {
+    const int r = j * 32 + (lane & 31);
+    char* row = region + r * 256 + 8 * (lane >> 5);
+    const int sw = col_swz(r);
+#pragma unroll
+    for (int i = 0; i < C::NBM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        store_vec4<OUT>(reinterpret_cast<OUT*>(row + (((4 * i + g) ^ sw) << 4)), acc[i][j][4 * g],
+                        acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+  }
+  if constexpr (TRANS) {
+#pragma unroll
+    for (int it = 0; it < C::WTN / 4; ++it) {
+      const int r = it * 4 + (lane >> 4), pc = lane & 15;
+      if (MASK && !((tmask >> ((pc >> 2) * C::NBN + (it >> 3))) & 1u)) continue;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(region + r * 256 + ((pc ^ col_swz(r)) << 4));
+      __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(out_t + (col0 + r) * ld_t + row0 + pc * 8));
+    }
+  }
+  if constexpr (ROWS) {
+    // every piece is read before the region is rewritten row by row (128-byte
+    // rows, pieces swizzled with the row), so that the stores are whole lines
+    constexpr int NH = C::WTN / 32, NI = C::WTM / 16;
+    const int l = lane & 15, half = (l & 3) >> 1, byte = 8 * (l & 1);
+    i16x8 v[NH][NI];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int ra = h * 32 + 8 * (lane >> 4) + (l >> 2), rb = ra + 4;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const i16x4 lo = lds_tr16(region + ra * 256 + (((2 * i + half) ^ col_swz(ra)) << 4) + byte);
+        const i16x4 hi = lds_tr16(region + rb * 256 + (((2 * i + half) ^ col_swz(rb)) << 4) + byte);
+        v[h][i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): every read has returned
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        *reinterpret_cast<i16x8*>(region + (16 * i + l) * 128 + (((4 * h + (lane >> 4)) ^ (l & 7)) << 4)) = v[h][i];
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // this wave's LDS writes have landed
+#pragma unroll
+    for (int it = 0; it < C::WTM / 8; ++it) {
+      const int r = it * 8 + (lane >> 3), pc = lane & 7;
+      if (MASK && !((rmask >> ((it >> 2) * C::NBN + (pc >> 2))) & 1u)) continue;
+      const f32x4 x = *reinterpret_cast<const f32x4*>(region + r * 128 + ((pc ^ (r & 7)) << 4));
+      __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(out_r + (row0 + r) * ld_r + col0 + pc * 8));
+    }
+  }
+}
+
 // The last B*X applies the update instead of storing O: the fp32 result is
 // staged through the wave's LDS region, 16 oriented rows at a time, as for a
 // row (wide matrix) or a transposed (tall matrix) store, and every 16-byte
@@ -429,12 +513,34 @@ __device__ __forceinline__ void store_w4(P* w, bool vec, int valid, const float 
   }
 }
 
+// What the update needs of its matrix, copied out of device memory before the K
+// loop (the update's stores could alias the descriptor, which would be read
+// again after each of them).
+struct ApplyDesc {
+  PtrEntry pe;
+  int32_t rows, cols, transposed, param_dtype;
+};
+
+// The whole block works on one matrix: its values go to scalar registers.
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T* uniform(T* ptr) {
+  const uint64_t v = reinterpret_cast<uint64_t>(ptr);
+  return reinterpret_cast<T*>(uint64_t(uint32_t(uniform(int32_t(v)))) |
+                              uint64_t(uint32_t(uniform(int32_t(v >> 32)))) << 32);
+}
+__device__ __forceinline__ ApplyDesc apply_desc(const PtrEntry* ptrs, const MatDev& d) {
+  const PtrEntry pe = ptrs[d.index];
+  return ApplyDesc{PtrEntry{uniform(pe.param), nullptr, nullptr, uniform(pe.out)}, uniform(d.rows), uniform(d.cols),
+                   uniform(d.transposed), uniform(d.param_dtype)};
+}
+
 // One pass: pieces it = 0..NP-1 of this lane, whose LDS offset, stored row
 // and stored column come from `at`.
 template <typename P, int NP, class At>
-__device__ __forceinline__ void apply_pass(const char* region, const PtrEntry& pe, const MatDev& d, float lrs,
+__device__ __forceinline__ void apply_pass(const char* region, const ApplyDesc& d, float lrs,
                                            float decay, int lane, At at) {
-  P* wbase = reinterpret_cast<P*>(pe.param);
+  P* wbase = reinterpret_cast<P*>(d.pe.param);
   const bool vec = (d.cols & 3) == 0;
   float w[NP][4];
 #pragma unroll
@@ -458,7 +564,7 @@ __device__ __forceinline__ void apply_pass(const char* region, const PtrEntry& p
 #pragma unroll
     for (int e = 0; e < 4; ++e) w[it][e] = fmaf(-lrs, o[e], w[it][e] * decay);
     store_w4<P>(wbase + row * d.cols + col, vec, valid, w[it]);
-    if (pe.out) store_w4<float>(pe.out + row * d.cols + col, vec, valid, o);
+    if (d.pe.out) store_w4<float>(d.pe.out + row * d.cols + col, vec, valid, o);
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // reads done before the region is rewritten
 }
@@ -514,7 +620,7 @@ struct ApplyLay {
 
 template <class C, bool TRANS, typename P>
 __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN], char* region,
-                                              const PtrEntry& pe, const MatDev& d, float lrs, float decay,
+                                              const ApplyDesc& d, float lrs, float decay,
                                               int64_t row0, int64_t col0, int lane) {
   using A = ApplyLay<C, TRANS>;
   const int64_t srow_end = TRANS ? col0 + C::WTN : row0 + C::WTM;
@@ -523,7 +629,7 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
     // bf16 W, whole wave tile inside W: every parameter load of the tile goes
     // out before the first update, so their latencies overlap
     typename Vec4<__bf16>::T w[A::NPASS][A::NP];
-    __bf16* wb = reinterpret_cast<__bf16*>(pe.param);
+    __bf16* wb = reinterpret_cast<__bf16*>(d.pe.param);
 #pragma unroll
     for (int pass = 0; pass < A::NPASS; ++pass)
 #pragma unroll
@@ -547,7 +653,7 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = __bf16(fmaf(-lrs, v[e], float(w[pass][it][e]) * decay));
         *reinterpret_cast<typename Vec4<__bf16>::T*>(wb + row * d.cols + col) = x;
-        if (pe.out) *reinterpret_cast<f32x4*>(pe.out + row * d.cols + col) = v;
+        if (d.pe.out) *reinterpret_cast<f32x4*>(d.pe.out + row * d.cols + col) = v;
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);
     }
@@ -556,7 +662,7 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
 #pragma unroll
   for (int pass = 0; pass < A::NPASS; ++pass) {
     A::stage(acc, region, pass >> 1, pass & 1, lane);
-    apply_pass<P, A::NP>(region, pe, d, lrs, decay, lane, [&](int piece, int& off, int64_t& row, int64_t& col) {
+    apply_pass<P, A::NP>(region, d, lrs, decay, lane, [&](int piece, int& off, int64_t& row, int64_t& col) {
       A::at(pass, piece, row0, col0, off, row, col);
     });
   }
@@ -566,20 +672,19 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
 // and parameter type.
 template <class C>
 __device__ __forceinline__ void apply_update_tile(const f32x16 (&acc)[C::NBM][C::NBN], char* region,
-                                                  const GemmArgs& args, const MatDev& d, int64_t row0, int64_t col0,
+                                                  const GemmArgs& args, const ApplyDesc& d, int64_t row0, int64_t col0,
                                                   int lane) {
-  const PtrEntry pe = args.ptrs[d.index];
   const float lrs = update_lr(args.lr, d.rows, d.cols);
   if (d.param_dtype == MUON_BF16) {
     if (d.transposed)
-      apply_via_lds<C, true, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+      apply_via_lds<C, true, __bf16>(acc, region, d, lrs, args.decay, row0, col0, lane);
     else
-      apply_via_lds<C, false, __bf16>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+      apply_via_lds<C, false, __bf16>(acc, region, d, lrs, args.decay, row0, col0, lane);
   } else {
     if (d.transposed)
-      apply_via_lds<C, true, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+      apply_via_lds<C, true, float>(acc, region, d, lrs, args.decay, row0, col0, lane);
     else
-      apply_via_lds<C, false, float>(acc, region, pe, d, lrs, args.decay, row0, col0, lane);
+      apply_via_lds<C, false, float>(acc, region, d, lrs, args.decay, row0, col0, lane);
   }
 }
 
@@ -595,13 +700,6 @@ __device__ __forceinline__ void apply_update_tile(const f32x16 (&acc)[C::NBM][C:
 // fragments.  32-byte segments of each LDS row are XOR-swizzled with the
 // row so that the 4 rows one 16-lane group touches fall in different banks.
 // ---------------------------------------------------------------------------
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef short i16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ i16x4 lds_tr16(const char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(p));
-}
-
 // Segment swizzle for row-major LDS rows of ROWB bytes: 32-byte segment s of
 // row r is stored at s ^ seg_swz(r).  A transposing read of one MFMA
 // fragment touches 4 consecutive rows (r & 3 = q) and two adjacent segments
@@ -854,6 +952,23 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
   // the epilogue's masked stores serve diagonal and half tiles
   const bool masked = htile || dtile;
   const int64_t mp = d.m_pad, np = d.n_pad;
+  // What the epilogue needs of the descriptor and the scale is loaded here: a
+  // load after the K loop, whose assembly the compiler moves no load across,
+  // would add its latency to every tile.
+  const int m = uniform(d.m);
+  ApplyDesc ad{};
+  if (STAGE == ST_BX && args.last) ad = apply_desc(args.ptrs, d);
+  const float sc = args.first ? args.scale[slot] : 1.f;
+  E* out_t = nullptr;        // transposed output (leading dimension mp)
+  E* out_r = nullptr;        // row-major output
+  int64_t ld_r = mp;
+  if (STAGE != ST_BX) {
+    out_t = reinterpret_cast<E*>(args.ws + d.sq_off[bo]);
+    out_r = out_t;
+  } else {
+    out_r = reinterpret_cast<E*>(args.ws + d.x_off[args.pin ^ 1]);
+    ld_r = np;
+  }
 
   const E* opa;
   const E* opb;
@@ -1001,22 +1116,9 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
   // rows of one column.  The outputs pass through the wave's private LDS
   // region (the stages are free after the K loop), so that every global
   // access is a full-line, 16-byte-per-lane row access.
-  const float sc = args.first ? args.scale[slot] : 1.f;
   const int64_t row0 = int64_t(ti) * TILE + wrow;
   const int64_t col0 = int64_t(tj) * TILE + wn * C::WTN;
   char* region = (wid < C::NW / 2 ? stage0 : stage1) + (wid % (C::NW / 2)) * C::WAVE_LDS;
-  E* out_t = nullptr;        // transposed output (leading dimension mp)
-  E* out_r = nullptr;        // row-major output
-  int64_t ld_r = mp;
-  bool rows_needed = true;
-  if (STAGE != ST_BX) {
-    out_t = reinterpret_cast<E*>(args.ws + d.sq_off[bo]);
-    out_r = out_t;
-    rows_needed = ti != tj;  // a diagonal tile is complete with one store
-  } else {
-    out_r = reinterpret_cast<E*>(args.ws + d.x_off[args.pin ^ 1]);
-    ld_r = np;
-  }
   if (STAGE == ST_POLY && ti == tj && args.diag != 0.f) {
     // diag * I on the real diagonal (the padding stays zero)
 #pragma unroll
@@ -1027,7 +1129,7 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
         for (int q = 0; q < 16; ++q) {
           const int r = wrow + 32 * i + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
           const int c = wn * C::WTN + 32 * j + (lane & 31);
-          if (r == c && ti * TILE + r < d.m) acc[i][j][q] += args.diag;
+          if (r == c && ti * TILE + r < m) acc[i][j][q] += args.diag;
         }
   }
   // Gram: oscale * s^2 * acc;  A*A: oscale * (acc + fcoef * A + diag * I);
@@ -1040,15 +1142,12 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] *= mul;
   if (STAGE == ST_BX && args.last) {
-    apply_update_tile<C>(acc, region, args, d, row0, col0, lane);
+    apply_update_tile<C>(acc, region, args, ad, row0, col0, lane);
   } else if (masked) {  // square outputs only
-    if (dlive) {
-      store_t_via_lds<C, E, true>(acc, region, out_t, mp, row0, col0, lane, bmask);
-      if (rmask) store_rows_via_lds<C, E, true>(acc, region, out_r, ld_r, row0, col0, lane, rmask);
-    }
+    if (dlive)
+      store_piece16<C, E, true, true, true>(acc, region, out_t, mp, out_r, ld_r, row0, col0, lane, bmask, rmask);
   } else {
-    if (!TRB) store_t_via_lds<C, E>(acc, region, out_t, mp, row0, col0, lane);
-    if (rows_needed) store_rows_via_lds<C, E>(acc, region, out_r, ld_r, row0, col0, lane);
+    store_piece16<C, E, STAGE != ST_BX, true, false>(acc, region, out_t, mp, out_r, ld_r, row0, col0, lane);
   }
 }
 

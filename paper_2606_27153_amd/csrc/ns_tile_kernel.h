@@ -66,6 +66,24 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
       }
   }
   const int64_t mp = d.m_pad, np = d.n_pad;
+  // What the epilogue needs of the descriptor and the scale is loaded here: a
+  // load after the K loop, whose assembly the compiler moves no load across,
+  // would add its latency to every tile.
+  const int m = uniform(d.m);
+  ApplyDesc ad{};
+  if (STAGE == ST_BX && args.last) ad = apply_desc(args.ptrs, d);
+  const float sc = args.first ? args.scale[slot] : 1.f;
+  E* out_t = nullptr;        // transposed output (leading dimension mp)
+  E* out_r = nullptr;        // row-major output
+  int64_t ld_r = mp;
+  if (STAGE != ST_BX) {
+    out_t = reinterpret_cast<E*>(args.ws + d.sq_off[bo]);
+    out_r = out_t;
+  } else {
+    out_t = TRB ? nullptr : reinterpret_cast<E*>(args.ws + d.xt_off[args.pin ^ 1]);
+    out_r = reinterpret_cast<E*>(args.ws + d.x_off[args.pin ^ 1]);
+    ld_r = np;
+  }
 
   const E* opa;
   const E* opb;
@@ -197,21 +215,9 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
   }
 
   // Epilogue, as in the 256-tile kernel.
-  const float sc = args.first ? args.scale[slot] : 1.f;
   const int64_t row0 = int64_t(ti) * TILE + wrow;
   const int64_t col0 = int64_t(tj) * TILE + wn * C::WTN;
   char* region = lds + wid * C::WAVE_LDS;
-  E* out_t = nullptr;        // transposed output (leading dimension mp)
-  E* out_r = nullptr;        // row-major output
-  int64_t ld_r = mp;
-  if (STAGE != ST_BX) {
-    out_t = reinterpret_cast<E*>(args.ws + d.sq_off[bo]);
-    out_r = out_t;
-  } else {
-    out_t = TRB ? nullptr : reinterpret_cast<E*>(args.ws + d.xt_off[args.pin ^ 1]);
-    out_r = reinterpret_cast<E*>(args.ws + d.x_off[args.pin ^ 1]);
-    ld_r = np;
-  }
   if (STAGE == ST_POLY && dtile && args.diag != 0.f) {
     // diag * I on the real diagonal (the padding stays zero)
 #pragma unroll
@@ -222,7 +228,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
         for (int q = 0; q < 16; ++q) {
           const int r = wrow + 32 * i + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
           const int c = wn * C::WTN + 32 * j + (lane & 31);
-          if (r == c && ti * TILE + r < d.m) acc[i][j][q] += args.diag;
+          if (r == c && ti * TILE + r < m) acc[i][j][q] += args.diag;
         }
   }
   const float mul = STAGE == ST_GRAM ? args.oscale * sc * sc : STAGE == ST_BX ? args.oscale * sc : args.oscale;
@@ -233,7 +239,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] *= mul;
   if (STAGE == ST_BX && args.last) {
-    apply_update_tile<C>(acc, region, args, d, row0, col0, lane);
+    apply_update_tile<C>(acc, region, args, ad, row0, col0, lane);
   } else if (dtile) {
     if (bmask) store_t_via_lds<C, E, true>(acc, region, out_t, mp, row0, col0, lane, bmask);
     if (rmask) store_rows_via_lds<C, E, true>(acc, region, out_r, ld_r, row0, col0, lane, rmask);
