@@ -77,8 +77,16 @@ def _kernel_patterns():
             if e == "f" and tile == 256:
                 continue
             for stage, kind in enumerate(("gram", "poly", "bx", "symm")):
-                pats.append((rf"ns_gemm_kernelI{e}Li{tile}ELi{wg}ELi{stage}E", f"{kind}:{cls}_t{tile}"))
-    return pats
+                key = f"{kind}:{cls}_t{tile}"
+                pats.append((rf"ns_gemm_kernelI{e}Li{tile}ELi{wg}ELi{stage}E", key))
+                if tile == 256:
+                    pats.append((rf"ns_gemm_kernelI{e}Li{stage}ELb", key))
+                else:
+                    pats.append((rf"ns_tile_kernelI{e}Li{tile}ELi{stage}ELi", key))
+                    if e == "f":
+                        pats.append((rf"ns_tile_kernel<float, {tile}, {stage}, ", key))
+    # (the profiler's demangler misreads <__bf16, 1, false>)
+    return pats + [(r"ns_gemm_kernel<bool _Accum", "poly:bf16_t256"), (r"ns_multi_kernel", "merged")]
 
 
 KERNEL_RE = _kernel_patterns() + [
