@@ -238,7 +238,7 @@ MUON_API muon_status muon_plan_matrix_info(muon_plan plan, int32_t index, muon_m
  * (lr, momentum_coef, weight_decay, ns_steps, nesterov) are captured by
  * value: a new value needs a new capture.  A call whose pointers differ
  * from the previous call's returns INVALID_ARG while its stream is being
- * captured (the copy from the ring could not be replayed safely).  A replay
+ * captured (a replay would hand over a table that may have changed since).  A replay
  * reads the device table as it is at replay time: step eagerly on other
  * buffers in between, and replays use those.
  * The plan must be used from the device it was created on.  The step checks
