@@ -597,6 +597,20 @@ struct ApplyLay {
       col = col0 + pc * 4;
     }
   }
+  // The element offset of piece lane + 64 * it of pass `pass` within a stored
+  // matrix of `cols` columns: lane_elem, the same for every piece and pass,
+  // plus a part that is uniform over the wave: origin for piece 0 of pass 0,
+  // and step(it) more from each piece to the next.
+  __device__ static __forceinline__ int64_t origin(int64_t row0, int64_t col0, int64_t cols) {
+    return TRANS ? col0 * cols + row0 : row0 * cols + col0;
+  }
+  __device__ static __forceinline__ int64_t step(int it, int64_t cols) {
+    if (!TRANS) return 64 / PPR * cols;
+    return it + 1 < NP ? 64 / PPR * cols : 16 - int64_t(64 / PPR * (NP - 1)) * cols;
+  }
+  __device__ static __forceinline__ uint32_t lane_elem(int lane, int cols) {
+    return uint32_t(lane / PPR) * uint32_t(cols) + uint32_t(lane % PPR * 4);
+  }
   // writes pass `pass` (half hh of MFMA block row i) of acc to the region
   __device__ static __forceinline__ void stage(const f32x16 (&acc)[C::NBM][C::NBN], char* region, int i, int hh,
                                                int lane) {
@@ -618,6 +632,19 @@ struct ApplyLay {
   }
 };
 
+// Widest stored row whose lane part (lane_elem: at most 15 rows and 12 columns)
+// stays below 2^32 bytes of fp32 O.
+constexpr int32_t kLaneCols = 1 << 26;
+
+// ptr + bytes, both uniform over the wave, as a value of its own in scalar
+// registers.
+template <typename T>
+__device__ __forceinline__ T advance(T ptr, int64_t bytes) {
+  ptr += bytes;
+  asm("" : "+s"(ptr));
+  return ptr;
+}
+
 template <class C, bool TRANS, typename P>
 __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN], char* region,
                                               const ApplyDesc& d, float lrs, float decay,
@@ -625,20 +652,31 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
   using A = ApplyLay<C, TRANS>;
   const int64_t srow_end = TRANS ? col0 + C::WTN : row0 + C::WTM;
   const int64_t scol_end = TRANS ? row0 + C::WTM : col0 + C::WTN;
-  if (__is_same(P, __bf16) && (d.cols & 3) == 0 && srow_end <= d.rows && scol_end <= d.cols) {
+  if (__is_same(P, __bf16) && (d.cols & 3) == 0 && srow_end <= d.rows && scol_end <= d.cols && d.cols < kLaneCols) {
     // bf16 W, whole wave tile inside W: every parameter load of the tile goes
-    // out before the first update, so their latencies overlap
-    typename Vec4<__bf16>::T w[A::NPASS][A::NP];
-    __bf16* wb = reinterpret_cast<__bf16*>(d.pe.param);
+    // out before the first update, so their latencies overlap.  A piece's
+    // address is a uniform pointer that walks over the pieces and one 32-bit
+    // lane offset for all of them (in global address space, whose accesses
+    // take the two apart).  Left to itself the compiler keeps a 64-bit lane
+    // address per piece from its load to its store, which next to the
+    // accumulators does not fit the 256 tile's registers (20 spilled, 84 bytes
+    // of scratch per lane; now 250 registers and none.  One 4096 x 4096 with O
+    // 1554 -> 1547 us, one 1B layer and four 8B layers the same).
+    typedef typename Vec4<__bf16>::T W4;
+    typedef __attribute__((address_space(1))) char* gptr;
+    W4 w[A::NPASS][A::NP];
+    const uint32_t lane_el = A::lane_elem(lane, d.cols);
+    const int64_t org = A::origin(row0, col0, d.cols);
+    gptr wp = (gptr)(d.pe.param) + org * 2;
 #pragma unroll
     for (int pass = 0; pass < A::NPASS; ++pass)
 #pragma unroll
       for (int it = 0; it < A::NP; ++it) {
-        int off;
-        int64_t row, col;
-        A::at(pass, lane + 64 * it, row0, col0, off, row, col);
-        w[pass][it] = *reinterpret_cast<const typename Vec4<__bf16>::T*>(wb + row * d.cols + col);
+        w[pass][it] = *(const __attribute__((address_space(1))) W4*)(wp + lane_el * 2);
+        wp = advance(wp, A::step(it, d.cols) * 2);
       }
+    wp = (gptr)(d.pe.param) + org * 2;
+    gptr op = d.pe.out ? (gptr)(d.pe.out) + org * 4 : nullptr;
 #pragma unroll
     for (int pass = 0; pass < A::NPASS; ++pass) {
       A::stage(acc, region, pass >> 1, pass & 1, lane);
@@ -649,11 +687,15 @@ __device__ __forceinline__ void apply_via_lds(const f32x16 (&acc)[C::NBM][C::NBN
         int64_t row, col;
         A::at(pass, lane + 64 * it, row0, col0, off, row, col);
         const f32x4 v = *reinterpret_cast<const f32x4*>(region + off);
-        typename Vec4<__bf16>::T x;
+        W4 x;
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = __bf16(fmaf(-lrs, v[e], float(w[pass][it][e]) * decay));
-        *reinterpret_cast<typename Vec4<__bf16>::T*>(wb + row * d.cols + col) = x;
-        if (d.pe.out) *reinterpret_cast<f32x4*>(d.pe.out + row * d.cols + col) = v;
+        *(__attribute__((address_space(1))) W4*)(wp + lane_el * 2) = x;
+        wp = advance(wp, A::step(it, d.cols) * 2);
+        if (d.pe.out) {
+          *(__attribute__((address_space(1))) f32x4*)(op + lane_el * 4) = v;
+          op = advance(op, A::step(it, d.cols) * 4);
+        }
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);
     }
