@@ -8,7 +8,6 @@
 // are advanced together instead of each paying a launch).
 #include <algorithm>
 #include <cmath>
-#include <functional>
 #include <map>
 #include <tuple>
 
@@ -232,7 +231,14 @@ double exec_time(const std::vector<TileLoad>& loads, int32_t exec) {
   const double slab16 = slab_time(kExec16[exec], total), slab32 = slab_time(kExec32[exec], total32);
   const ExecModel& any = kExec16[exec];
   const int64_t slots = std::min(total, kCus * any.occ);
-  std::vector<double> heap(size_t(slots), 0.0);  // min-heap of slot end times
+  // The slots, grouped by the time at which they become free, soonest first.
+  // Tiles of one length that go to a group leave it as one group again, so a
+  // run of matrices costs a step per group and round, not one per tile.
+  struct Slots {
+    double free;
+    int64_t n;
+  };
+  std::vector<Slots> groups{{0.0, slots}};
   double end = 0;
   for (size_t i = 0; i < loads.size();) {
     const int64_t slabs = loads[i].slabs;
@@ -243,14 +249,20 @@ double exec_time(const std::vector<TileLoad>& loads, int32_t exec) {
     // all but the last two rounds of a long run level out over the slots
     if (n > 2 * slots) {
       const int64_t rounds = n / slots - 1;
-      for (double& h : heap) h += double(rounds) * dt;
+      for (Slots& g : groups) g.free += double(rounds) * dt;
       n -= rounds * slots;
     }
-    for (; n > 0; --n) {
-      std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
-      heap.back() += dt;
-      end = std::max(end, heap.back());
-      std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+    while (n > 0) {
+      const Slots busy{groups[0].free + dt, std::min(n, groups[0].n)};
+      n -= busy.n;
+      end = std::max(end, busy.free);
+      if ((groups[0].n -= busy.n) == 0) groups.erase(groups.begin());
+      auto at = groups.begin();
+      while (at != groups.end() && at->free < busy.free) ++at;
+      if (at != groups.end() && at->free == busy.free)
+        at->n += busy.n;
+      else
+        groups.insert(at, busy);
     }
   }
   return any.start + end;
@@ -321,9 +333,22 @@ int32_t wave_mode(const Plan& p, const WaveHost& w, const std::vector<GroupLoads
       line_launches += o.n;
     }
   }
+  // A merged launch is set by the stages its two forms have reached; a chain
+  // has far fewer combinations of them than launches, so each is estimated once.
   auto merged_us = [&](bool sides_only) {
+    std::map<std::pair<int32_t, int32_t>, double> known;
+    auto stage_at = [&](int32_t form, int32_t t) {
+      const OpList& o = list[form];
+      return t >= o.n ? -1 : o.op[t].stage == ST_SYM ? int32_t(ST_POLY) : o.op[t].stage;
+    };
     double us = 0;
     for (int32_t t = 0; t < (sides_only ? side_len : len); ++t) {
+      const auto found = known.emplace(std::make_pair(stage_at(0, t), stage_at(1, t)), 0.0);
+      double& launch_us = found.first->second;
+      if (!found.second) {
+        us += launch_us;
+        continue;
+      }
       std::vector<TileLoad> all;
       for (size_t i = 0; i < n; ++i) {
         const OpList& o = list[w.launches[i].gram];
@@ -331,7 +356,8 @@ int32_t wave_mode(const Plan& p, const WaveHost& w, const std::vector<GroupLoads
         const std::vector<TileLoad>& l = groups[i].of(o.op[t].stage);
         all.insert(all.end(), l.begin(), l.end());
       }
-      us += exec_time(all, EX_64_RING3);
+      launch_us = exec_time(all, EX_64_RING3);
+      us += launch_us;
     }
     return us;
   };

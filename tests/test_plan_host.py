@@ -58,3 +58,27 @@ def test_ragged_and_random_plans(plan_check):
     for trial in range(5):
         shapes = [(int(rng.integers(1, 3000)), int(rng.integers(1, 3000))) for _ in range(40)]
         _run(plan_check, shapes, wave_bytes=int(rng.integers(1, 4)) << 28)
+
+
+# a plan is built inside the first step of an optimizer: a few layers must not
+# cost more than that step.  The bounds are several times what the planner
+# takes (30 to 300 us) and a fraction of what simulating every tile of every
+# candidate launch took (500 to 1900 us)
+@pytest.mark.parametrize("shapes,limit_us", [
+    ([(1024, 1024)] * 2 + [(1024, 256)] * 2 + [(1024, 2816)] * 2 + [(2816, 1024)], 250),
+    ([(2048, 2048)] * 2 + [(2048, 512)] * 2 + [(2048, 5632)] * 2 + [(5632, 2048)], 300),
+    ([(65, 200), (200, 65), (130, 700), (700, 130), (257, 513), (513, 257), (1000, 1000), (96, 4304), (7, 13),
+      (1152, 1200), (300, 300)], 250),
+    ([(r, c) for r in (32, 64, 128, 256) for c in (512, 1024) for _ in range(25)], 900)])
+def test_planning_is_cheap(shapes, limit_us):
+    import time
+
+    from paper_2606_27153_amd.optim import MuonPlan
+    descs = [(r, c, "bf16", "bf16") for r, c in shapes]
+    best = float("inf")
+    for _ in range(40):
+        t0 = time.perf_counter()
+        plan = MuonPlan(descs, host_only=True)
+        best = min(best, time.perf_counter() - t0)
+        plan.close()
+    assert best * 1e6 < limit_us
