@@ -9,9 +9,13 @@ Here the candidates are the output tiles the operand type offers (256, 128,
 64 for 16-bit operands; 128, 64 for fp32).  A shape is not timed alone:
 matrices of one kernel class share grouped launches, so a tile that wins for
 a shape in isolation (more blocks for a small batch) can lose inside the
-whole set, where the batch is already full.  The tuner therefore times whole
-steps of a reduced copy of the set (each shape at most ``max_per_shape``
-times, keeping the mix) and runs one pass of coordinate descent from the
+whole set, where the batch is already full.  A hint is the tile of launches
+that fill the chip, and sets the padding; a launch of at most
+``CLASS_TILE_LAUNCH`` tiles may run on smaller ones whatever the hint says.
+The tuner therefore times whole steps of a reduced copy of the set (each shape
+at most ``max_per_shape`` times, keeping the mix, but often enough that
+launches which are on their class's tile in the full set are on it in the copy
+too) and runs one pass of coordinate descent from the
 planner's own cost-model choice: for each shape, heaviest first, each other
 tile is tried with the rest fixed and kept if the step gets faster by more
 than ``min_gain``.  The result can only match or beat the cost model on the
@@ -32,7 +36,12 @@ import statistics
 from typing import Callable, Dict, List, Optional, Sequence
 
 CACHE_ENV = "MUON_TUNE_CACHE"
-TUNER_VERSION = 2
+# part of the cache key: raised when the kernels or the meaning of a hint change,
+# so that choices measured before are measured again (3: hints set the padding
+# and the tile of full launches only)
+TUNER_VERSION = 3
+CLASS_TILE_LAUNCH = 1024   # launches of more class tiles always run on them (kExecMaxTiles in plan.cpp)
+GRAM_MIN_M = 256           # smaller matrices stay on Eq. 2
 
 
 def default_cache_path() -> str:
@@ -59,6 +68,38 @@ def set_key(groups: Dict[tuple, List[int]], *, precision: str, gram_min_aspect: 
     digest = hashlib.sha256(sig.encode()).hexdigest()[:16]
     return (f"v{TUNER_VERSION}|{device}|abi{abi}|{precision}|aspect{gram_min_aspect:g}|k{ns_steps}|"
             f"cap{max_per_shape}|{digest}")
+
+
+def kept_copies(groups: Dict[tuple, List[int]], *, precision: str, gram_min_aspect: float,
+                max_per_shape: int) -> Dict[tuple, int]:
+    """How many matrices of each shape the reduced set keeps: at most
+    ``max_per_shape``, raised where the launches of a group of shapes (one
+    operand type and iteration form) are on their class's tile in the full set
+    and would no longer be with that many.  Counted on the largest tile, which
+    has the fewest."""
+    parts: Dict[tuple, List[tuple]] = {}
+    for g in groups:
+        m, n = min(g[0], g[1]), max(g[0], g[1])
+        fp32 = 256 not in candidate_tiles(g[0], g[1], precision)
+        gram = not fp32 and gram_min_aspect > 0 and m >= GRAM_MIN_M and n >= gram_min_aspect * m
+        parts.setdefault((fp32, gram), []).append(g)
+    kept: Dict[tuple, int] = {}
+    for (fp32, _), shapes in parts.items():
+        tile = 128 if fp32 else 256
+
+        def launches(cap):   # tiles of the square products and of B*X
+            low = full = 0
+            for g in shapes:
+                a, b = -(-min(g[0], g[1]) // tile), -(-max(g[0], g[1]) // tile)
+                k = min(len(groups[g]), cap)
+                low, full = low + k * a * (a + 1) // 2, full + k * a * b
+            return low, full
+        whole = launches(max(len(groups[g]) for g in shapes))
+        cap = max_per_shape
+        while any(f > CLASS_TILE_LAUNCH >= r for f, r in zip(whole, launches(cap))):
+            cap += 1
+        kept.update((g, min(len(groups[g]), cap)) for g in shapes)
+    return kept
 
 
 class TileCache:
@@ -169,11 +210,13 @@ def tune(descs: Sequence, *, precision: str = "bf16", gram_min_aspect: float = 1
         order = list(groups)
         base = planner_tiles([tuple(g) for g in order], precision=precision, gram_min_aspect=gram_min_aspect)
         choice = dict(zip(order, base))
+        kept = kept_copies(groups, precision=precision, gram_min_aspect=gram_min_aspect,
+                           max_per_shape=max_per_shape)
 
         def reduced(ch):
             out = []
             for g in order:
-                out += [tuple(g) + (ch[g],)] * min(len(groups[g]), max_per_shape)
+                out += [tuple(g) + (ch[g],)] * kept[g]
             return out
         base_ms = best = float(timer(reduced(choice)))
         # heaviest shapes first (m^2 n per matrix times the count)

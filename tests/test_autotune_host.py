@@ -81,3 +81,60 @@ def test_bad_tile_hints(lib, desc, hint, status):
     h = ctypes.c_void_p()
     assert lib.muon_plan_create(arr, 1, ctypes.byref(opts), ctypes.byref(h)) == status
     assert "tile_hint" in L.last_error()
+
+
+def test_choices_of_older_kernels_are_measured_again(tmp_path):
+    # an entry written by version 2 of the tuner (hints forced every launch's
+    # tile) for the same set is not served
+    descs = [(300, 900, "bf16", "bf16")] * 3
+    path = tmp_path / "tiles.json"
+    kw = dict(precision="bf16", cache_path=str(path), device_name="dev", abi=3)
+    calls = []
+
+    def timer(ds):
+        calls.append(1)
+        return 1.0
+    T.tune(descs, timer=timer, **kw)
+    data = json.loads(path.read_text())
+    (key, entry), = data.items()
+    old = key.replace(f"v{T.TUNER_VERSION}|", "v2|")
+    assert old != key
+    path.write_text(json.dumps({old: {**entry, "tiles": {k: 64 for k in entry["tiles"]}}}))
+    calls.clear()
+    assert T.tune(descs, timer=timer, **kw) == [int(v) for v in entry["tiles"].values()] * 3 and calls
+
+
+def _tiles(shapes, tile):
+    low = full = 0
+    for (r, c), k in shapes:
+        a, b = -(-min(r, c) // tile), -(-max(r, c) // tile)
+        low, full = low + k * a * (a + 1) // 2, full + k * a * b
+    return low, full
+
+
+@pytest.mark.parametrize("shapes,precision", [
+    ({(2048, 1408): 256, (1408, 2048): 128}, "bf16"),                    # expert bank: fills the chip, 16 + 16 do not
+    ({(1152, 3456): 27, (1152, 4304): 27, (4304, 1152): 27}, "bf16"),    # the vision tower's Gram-space matrices
+    ({(2048, 2048): 32, (2048, 512): 32}, "fp16"),
+    ({(512, 32): 20}, "bf16"), ({(64, 512): 300, (40, 1024): 200}, "bf16"), ({(4096, 4096): 64}, "fp32"),
+    ({(256, 300): 40, (700, 256): 900}, "bf16")])
+def test_reduced_set_launches_like_the_full_one(shapes, precision):
+    # a group's launches leave their class's tile (at most 1024 of them) in the
+    # reduced set only where they do in the full one
+    groups, i = {}, 0
+    for (r, c), k in shapes.items():
+        groups[(r, c, "bf16", "bf16")] = list(range(i, i + k))
+        i += k
+    kept = T.kept_copies(groups, precision=precision, gram_min_aspect=1.4, max_per_shape=16)
+    by = {}
+    for (r, c, _, _), ix in groups.items():
+        m, n = min(r, c), max(r, c)
+        fp32 = precision == "fp32" or (precision == "bf16" and m <= 64)
+        gram = not fp32 and m >= 256 and n >= 1.4 * m
+        by.setdefault((fp32, gram), []).append(((r, c), len(ix), kept[(r, c, "bf16", "bf16")]))
+    for (fp32, _), g in by.items():
+        tile = 128 if fp32 else 256
+        full = _tiles([(s, n) for s, n, _ in g], tile)
+        red = _tiles([(s, k) for s, _, k in g], tile)
+        assert [v > 1024 for v in full] == [v > 1024 for v in red]
+        assert all(k >= min(n, 16) for _, n, k in g)
