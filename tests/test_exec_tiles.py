@@ -157,3 +157,26 @@ def test_groups_run_together_match_each_matrix_alone(wave, precision):
         check(grads, f"replay {replay}")
     for q in plans + [plan]:
         q.close()
+
+
+# enough matrices with a half tile (m padded to 128 past a multiple of 256) that
+# the square products of both forms stay on the 256 tile
+HALF_SET = [(1152, 1700)] * 36 + [(1700, 1152)] * 36 + [(640, 640)] * 180
+
+
+@pytest.mark.parametrize("precision", [0, 2])
+def test_half_tile_set_stays_on_the_256_tile(lists_check, precision):
+    # three kinds of launch for each of the two groups, no small-tile list
+    assert _run(lists_check, HALF_SET, precision)[:4] == [6, 0, 0, 0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["bf16", "fp16"])
+def test_half_tiles_match_the_oracle(precision):
+    from parity_utils import assert_parity, run_parity
+    wl = custom_workload(HALF_SET, seed=74)
+    plan = MuonPlan([(m.rows, m.cols, m.param, m.grad) for m in wl.matrices], precision=precision)
+    assert [plan.matrix_info(i)["m_pad"] for i in (0, 71, 72)] == [1152, 1152, 640]
+    res = run_parity(wl, precision=precision, steps=1, plan=plan, check=[0, 71, 72, 251])
+    plan.close()
+    assert_parity(res, precision, "half tiles on the 256 tile")
