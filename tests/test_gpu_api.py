@@ -303,6 +303,51 @@ def test_moving_grad_buffers_match_fixed_ones_bitwise():
     moving.close()
 
 
+# up to 112 matrices the pointer table travels in the momentum launches, more
+# through the plan's pinned ring of 8 slots; small waves put several multi-group
+# waves behind one table
+@pytest.mark.parametrize("n,wave_bytes", [(112, 0), (112, 8 << 20), (113, 0), (130, 8 << 20)])
+def test_pointer_table_of_either_kind_follows_moving_buffers(n, wave_bytes):
+    # 20 steps enqueued ahead of the GPU, each with other gradient and parameter
+    # buffers and other missing gradients, so that ring slots come round while
+    # their copies are still queued; bitwise as steps that each run on a fresh
+    # plan (whose one table is its first) and are waited for
+    shapes = [(64, 128), (128, 64), (96, 160), (256, 384), (40, 72)]
+    wl = custom_workload([shapes[i % len(shapes)] for i in range(n)], seed=31)
+    descs = [(m.rows, m.cols, m.param, m.grad) for m in wl.matrices]
+    kw = dict(lr=0.02, momentum=0.95, weight_decay=0.01, ns_steps=5)
+    dev, steps = "cuda:0", 20
+    pa, ma = make_state(torch, wl, dev)
+    pb, mb = make_state(torch, wl, dev)
+    base = make_grads(torch, wl, 0, dev)
+    grads = [[None if (i + s) % 7 == 0 else g * (1.0 + 0.25 * s) for i, g in enumerate(base)] for s in range(steps)]
+    twin = [p.clone() for p in pb]           # the parameters alternate between two sets of buffers
+    plan = MuonPlan(descs, wave_bytes=wave_bytes)
+    if wave_bytes:
+        assert plan.info()["n_waves"] >= 4
+    ws = plan.workspace(dev)
+    big = torch.randn(8192, 8192, device=dev, dtype=torch.bfloat16)
+    out = torch.empty_like(big)
+    torch.cuda.synchronize()
+    for _ in range(30):                      # tens of ms in which the host gets ahead
+        torch.mm(big, big, out=out)
+    cur, nxt = pb, twin
+    for s in range(steps):
+        plan.step(cur, grads[s], mb, workspace=ws, **kw)
+        for x, y in zip(nxt, cur):
+            x.copy_(y)
+        cur, nxt = nxt, cur
+    torch.cuda.synchronize()
+    for s in range(steps):
+        ref = MuonPlan(descs, wave_bytes=wave_bytes)
+        ref.step(pa, grads[s], ma, **kw)
+        torch.cuda.synchronize()
+        ref.close()
+    for i, (x, y) in enumerate(zip(pa + ma, cur + mb)):
+        assert torch.equal(x, y), (i % n, descs[i % n])
+    plan.close()
+
+
 def test_moving_grad_buffers_cost_no_host_sync():
     # tiny set: steps alternating between two grad buffer sets (a pointer
     # refresh every step) take about as long as steps on one set
