@@ -7,10 +7,12 @@
 A step is one muon_step over every matrix of the chosen synthetic set:
 momentum + Nesterov, Frobenius normalisation, 5 Newton-Schulz steps, apply.
 Inputs (params, grads, momentum) are resident in HBM before the timed
-region.  Per-launch durations come from HIP events recorded by the library
-on its stream during the timed steps; the dominant kernel's achieved rate is
-its algorithmic work per launch over its mean launch duration.  The fp64
-oracle is timed on the host cores on a bounded sample as a reference point.
+region.  The timed steps run as a caller's do, without launch timing.
+Per-launch durations come from HIP events recorded by the library on its
+stream in further steps (--split-steps), in which every group runs its own
+launches one after another; the dominant kernel's achieved rate is its
+algorithmic work per launch over its mean launch duration.  The fp64 oracle
+is timed on the host cores on a bounded sample as a reference point.
 """
 from __future__ import annotations
 
@@ -73,12 +75,11 @@ def read_traffic(kernel_key: str, path: str = TRAFFIC_SUMMARY):
 def _kernel_patterns():
     pats = []
     for e, cls in (("DF16b", "bf16"), ("f", "f32"), ("DF16_", "f16")):
-        for tile, wg in ((256, "2ELi4"), (128, "2ELi2"), (64, "2ELi2")):
+        for tile in (256, 128, 64):
             if e == "f" and tile == 256:
                 continue
             for stage, kind in enumerate(("gram", "poly", "bx", "symm")):
                 key = f"{kind}:{cls}_t{tile}"
-                pats.append((rf"ns_gemm_kernelI{e}Li{tile}ELi{wg}ELi{stage}E", key))
                 if tile == 256:
                     pats.append((rf"ns_gemm_kernelI{e}Li{stage}ELb", key))
                 else:
@@ -529,6 +530,9 @@ def main(argv=None) -> int:
                     help="Gram-space recurrence (Eq. 4) for matrices with n >= this * m; 0 = Eq. 2 only")
     ap.add_argument("--cpu-budget", type=float, default=20.0, help="seconds of oracle time to sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--split-steps", type=int, default=None, metavar="N",
+                    help="steps with launch timing after the timed ones, for the split by kernel (default: as many "
+                         "as are timed, at most 10); 0 traces the schedule of the timed steps alone")
     ap.add_argument("--no-peaks", action="store_true", help="skip the copy and vendor-BLAS reference rates")
     ap.add_argument("--copy-calibration-mib", type=int, default=0,
                     help="run one device-to-device copy of this size first (HBM counter calibration)")
@@ -609,7 +613,7 @@ def main(argv=None) -> int:
                     gram_min_aspect=args.gram_min_aspect)
     info = plan.info()
     log(f"[bench] plan: {info['n_waves']} waves, {info['n_buckets']} buckets, "
-        f"{info['launches_per_step']} launches/step at max steps, workspace {info['workspace_bytes'] / 2**30:.2f} GiB")
+        f"at most {info['launches_per_step']} launches/step at max steps, workspace {info['workspace_bytes'] / 2**30:.2f} GiB")
     if args.copy_calibration_mib > 0:
         nb = args.copy_calibration_mib << 20
         src = torch.ones(nb, dtype=torch.uint8, device=dev)
@@ -631,12 +635,17 @@ def main(argv=None) -> int:
         torch.cuda.synchronize()
         log(f"[bench] warmup step {i + 1}/{args.warmup} done")
 
+    ms_per_step, per_step = time_steps(plan, params, grads, moms, kw, 0, args.steps)
+    log(f"[bench] {args.steps} timed steps: {ms_per_step:.3f} ms/step")
+    # the split by kernel: steps with launch timing on (outside the timed region)
+    split = min(args.steps, 10) if args.split_steps is None else args.split_steps
     plan.set_timing(True)
     plan.timing_read(reset=True)
-    ms_per_step, per_step = time_steps(plan, params, grads, moms, kw, 0, args.steps)
+    split_ms = time_steps(plan, params, grads, moms, kw, 0, split)[0] if split else None
     plan.set_timing(False)
     stats = plan.timing_read(reset=True)
-    log(f"[bench] {args.steps} timed steps: {ms_per_step:.3f} ms/step")
+    if split:
+        log(f"[bench] {split} steps with launch timing: {split_ms:.3f} ms/step")
     zero = [m.zero_grad for m in wl.matrices]
     if any(zero):
         flop_share = live_flop_share(plan, wl.ns_steps, zero)
@@ -649,8 +658,8 @@ def main(argv=None) -> int:
     per_kernel = []
     for s in sorted(stats, key=lambda s: -s["total_ms"]):
         mean_ms = s["total_ms"] / max(1, s["launches"])
-        row = {"kind": s["kind"], "class": s["kernel_class"], "launches_per_step": s["launches"] / args.steps,
-               "ms_per_step": round(s["total_ms"] / args.steps, 4), "mean_launch_ms": round(mean_ms, 5)}
+        row = {"kind": s["kind"], "class": s["kernel_class"], "launches_per_step": s["launches"] / split,
+               "ms_per_step": round(s["total_ms"] / split, 4), "mean_launch_ms": round(mean_ms, 5)}
         if s["kind"] in GEMM_KINDS and s["total_ms"] > 0:
             row["tflops"] = round(s["algo_flops"] / (s["total_ms"] * 1e-3) / 1e12, 2)
         if s["kind"] in ("momentum", "apply") and s["total_ms"] > 0:
@@ -659,38 +668,40 @@ def main(argv=None) -> int:
         log(f"[bench]   {json.dumps(row)}")
 
     gemm = [s for s in stats if s["kind"] in GEMM_KINDS]
-    gemm_ms = sum(s["total_ms"] for s in gemm) / args.steps
-    gemm_flops = sum(s["algo_flops"] for s in gemm) / args.steps
+    gemm_ms = sum(s["total_ms"] for s in gemm) / max(1, split)
+    gemm_flops = sum(s["algo_flops"] for s in gemm) / max(1, split)
     ew = [s for s in stats if s["kind"] in ("momentum", "apply")]
-    ew_bytes = sum(s["algo_bytes"] for s in ew) / args.steps
+    ew_bytes = sum(s["algo_bytes"] for s in ew) / max(1, split)
     ns_tflops = gemm_flops / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
     mfma_util = 100.0 * ns_tflops / peak_mm
     eq2_flops = sum(eq2_work_flops(m.rows, m.cols, wl.ns_steps) for m in wl.matrices if not m.zero_grad)
     eq2_tflops = eq2_flops / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
 
-    dom = max(stats, key=lambda s: s["total_ms"])
-    dom_key = f"{dom['kind']}:{dom['kernel_class']}"
-    dom_mean_s = dom["total_ms"] * 1e-3 / dom["launches"]
-    if dom["kind"] in GEMM_KINDS:
-        achieved = dom["algo_flops"] / dom["launches"] / dom_mean_s / 1e12
-        roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak_mm, "unit": "TFLOP/s",
-                "frac": round(achieved / peak_mm, 4)}
-    else:
-        achieved = dom["algo_bytes"] / dom["launches"] / dom_mean_s / 1e9
-        roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "frac": round(achieved / PEAK_HBM_GBS, 4)}
-    roof["kernel"] = dom_key
-    roof["mean_launch_ms"] = round(dom["total_ms"] / dom["launches"], 4)
-    traffic = read_traffic(dom_key)
-    roof["traffic"] = None if traffic is None else round(traffic)
-    if dom["kind"] in GEMM_KINDS:
-        launches_per_step = dom["launches"] / args.steps
-        alg = gemm_algorithmic_bytes(plan, wl.ns_steps, dom["kind"], dom["kernel_class"],
-                                     [2 if m.param == "bf16" else 4 for m in wl.matrices])
-        roof["algorithmic_bytes"] = round(alg / launches_per_step)
-        roof["flop_per_byte"] = round(dom["algo_flops"] / dom["launches"] / roof["algorithmic_bytes"], 1)
-        if traffic is not None:
-            roof["traffic_vs_algorithmic"] = round(traffic / roof["algorithmic_bytes"], 2)
+    roof = None
+    if stats:
+        dom = max(stats, key=lambda s: s["total_ms"])
+        dom_key = f"{dom['kind']}:{dom['kernel_class']}"
+        dom_mean_s = dom["total_ms"] * 1e-3 / dom["launches"]
+        if dom["kind"] in GEMM_KINDS:
+            achieved = dom["algo_flops"] / dom["launches"] / dom_mean_s / 1e12
+            roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak_mm, "unit": "TFLOP/s",
+                    "frac": round(achieved / peak_mm, 4)}
+        else:
+            achieved = dom["algo_bytes"] / dom["launches"] / dom_mean_s / 1e9
+            roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                    "frac": round(achieved / PEAK_HBM_GBS, 4)}
+        roof["kernel"] = dom_key
+        roof["mean_launch_ms"] = round(dom["total_ms"] / dom["launches"], 4)
+        traffic = read_traffic(dom_key)
+        roof["traffic"] = None if traffic is None else round(traffic)
+        if dom["kind"] in GEMM_KINDS:
+            launches_per_step = dom["launches"] / split
+            alg = gemm_algorithmic_bytes(plan, wl.ns_steps, dom["kind"], dom["kernel_class"],
+                                         [2 if m.param == "bf16" else 4 for m in wl.matrices])
+            roof["algorithmic_bytes"] = round(alg / launches_per_step)
+            roof["flop_per_byte"] = round(dom["algo_flops"] / dom["launches"] / roof["algorithmic_bytes"], 1)
+            if traffic is not None:
+                roof["traffic_vs_algorithmic"] = round(traffic / roof["algorithmic_bytes"], 2)
 
     graph_ms = None
     if args.graph:
@@ -714,7 +725,7 @@ def main(argv=None) -> int:
     if not args.no_peaks and args.copy_calibration_mib == 0:
         peaks = measure_peaks(torch, dev)
         log(f"[bench] measured on this box: {peaks}")
-        if roof["bound"] == "mfma" and args.precision != "fp32":
+        if roof and roof["bound"] == "mfma" and args.precision != "fp32":
             # the dominant kernel against the vendor BLAS on the same box
             # (box-to-box clock differences move both alike)
             roof["vs_vendor_bf16_bmm"] = round(roof["achieved"] / peaks["bf16_bmm_tflops"], 3)
@@ -743,17 +754,19 @@ def main(argv=None) -> int:
                    "params": sorted({m.param for m in wl.matrices}), "momentum": "f32",
                    "ns_operands": args.precision, "gram_space_matrices": info["n_gram"],
                    "gram_min_aspect": args.gram_min_aspect, "autotune": tuned, "parallelism": "single GPU"},
-        "mfma_util_pct_ns_gemms": round(mfma_util, 2),
-        "ns_gemm_tflops": round(ns_tflops, 2),
-        "ns_gemm_ms_per_step": round(gemm_ms, 3),
-        "ns_eq2_work_tflops": round(eq2_tflops, 2),
-        "ns_eq2_work_pct_of_peak": round(100.0 * eq2_tflops / peak_mm, 2),
+        "mfma_util_pct_ns_gemms": round(mfma_util, 2) if split else None,
+        "ns_gemm_tflops": round(ns_tflops, 2) if split else None,
+        "ns_gemm_ms_per_step": round(gemm_ms, 3) if split else None,
+        "ns_eq2_work_tflops": round(eq2_tflops, 2) if split else None,
+        "ns_eq2_work_pct_of_peak": round(100.0 * eq2_tflops / peak_mm, 2) if split else None,
         "graph_ms_per_step": None if graph_ms is None else round(graph_ms, 3),
         "step_ms_median": round(percentile(per_step, 0.5), 3),
         "step_ms_p10": round(percentile(per_step, 0.1), 3),
         "step_ms_p90": round(percentile(per_step, 0.9), 3),
-        "step_roofline_floor_ms": round(floor_ms, 3),
-        "step_roofline_frac": round(floor_ms / ms_per_step, 4),
+        "split_steps": split,
+        "split_ms_per_step": None if split_ms is None else round(split_ms, 3),
+        "step_roofline_floor_ms": round(floor_ms, 3) if split else None,
+        "step_roofline_frac": round(floor_ms / ms_per_step, 4) if split else None,
         "roofline": roof,
         "measured_peaks": peaks,
         "cpu_baseline": cpu,

@@ -45,11 +45,11 @@ def test_gemm_algorithmic_bytes(lib, aspect):
 
 
 def test_kernel_keys():
-    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16bLi256ELi2ELi4ELi3EEEvNS0_8GemmArgsE") \
+    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16bLi3ELb0EEEvNS_8GemmArgsE") \
         == "symm:bf16_t256"
-    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIfLi64ELi2ELi2ELi2EEEvNS0_8GemmArgsE") \
+    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_tile_kernelIfLi64ELi2ELi3EEEvNS_8GemmArgsE") \
         == "bx:f32_t64"
-    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16_Li256ELi2ELi4ELi2EEEvNS0_8GemmArgsE") \
+    assert bench.kernel_key("_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16_Li2ELb1EEEvNS_8GemmArgsE") \
         == "bx:f16_t256"
     assert bench.kernel_key("muon::(anonymous namespace)::apply_kernel(...)") == "apply"
 
@@ -57,7 +57,7 @@ def test_kernel_keys():
 def test_traffic_summary_round_trip(tmp_path):
     # counter files as rocprofv3 writes them: a 1 MiB copy reads 512 KiB and
     # writes 1024 KiB by the counters, so the scales are 2 and 1
-    sym = "_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16bLi256ELi2ELi4ELi3EEEvNS0_8GemmArgsE"
+    sym = "_ZN4muon12_GLOBAL__N_114ns_gemm_kernelIDF16bLi3ELb0EEEvNS_8GemmArgsE"
     rows = [("__amd_rocclr_copyBuffer", "FETCH_SIZE", 512.0), ("__amd_rocclr_copyBuffer", "WRITE_SIZE", 1024.0),
             (sym, "FETCH_SIZE", 100.0), (sym, "FETCH_SIZE", 300.0), (sym, "WRITE_SIZE", 50.0)]
     d = tmp_path / "pmc"

@@ -513,3 +513,17 @@ def test_capture_with_moved_buffers_is_refused():
     torch.cuda.synchronize()
     assert not torch.equal(p[0], before[0])
     plan.close()
+
+
+def test_bench_times_the_schedule_a_caller_gets(capsys):
+    # the tiny set's groups share launches in an ordinary step (about 0.12 ms) and
+    # run apart, event by event, with launch timing on (about 0.4 ms): the reported
+    # value is the former, the split by kernel comes from the latter
+    import json
+
+    import bench
+    assert bench.main(["--config", "tiny", "--steps", "30", "--warmup", "5", "--no-cpu-baseline", "--no-peaks"]) == 0
+    line = json.loads(capsys.readouterr().out.strip().splitlines()[-1])
+    assert line["steps"] == 30 and line["value"] == line["ms_per_step"]
+    assert line["value"] < 0.7 * line["split_ms_per_step"]
+    assert {k["kind"] for k in line["kernels"]} >= {"momentum", "finalize", "gram", "poly", "bx"}

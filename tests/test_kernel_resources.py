@@ -6,6 +6,7 @@ import os
 import re
 import subprocess
 
+import bench
 from paper_2606_27153_amd.build import LIB_PATH
 
 READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
@@ -36,3 +37,11 @@ def test_no_kernel_spills(tmp_path):
     assert any("ns_tile_kernel" in k for k in kernels) and any("momentum_kernel" in k for k in kernels)
     bad = {k: v for k, v in kernels.items() if v["private_segment_fixed_size"] or v["vgpr_spill_count"]}
     assert not bad, bad
+
+
+def test_profile_summaries_name_every_kernel(tmp_path):
+    # the summaries' names of the kernels come from their mangled names
+    keys = {k: bench.kernel_key(k) for k in _kernels(tmp_path)}
+    assert not {k for k, v in keys.items() if v.startswith("other")}, keys
+    assert sorted(v for k, v in keys.items() if "ns_gemm_kernel" in k) == sorted(
+        2 * [f"{s}:{e}_t256" for s in ("gram", "poly", "bx", "symm") for e in ("bf16", "f16")])
