@@ -199,10 +199,8 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
       // issued after it are in flight; the barrier publishes it and retires
       // the stage that was read in the previous trip
       const int after = nk - 1 - kt < NST - 2 ? nk - 1 - kt : NST - 2;
-      static_assert(NST >= 2 && NST <= 4, "waits below cover two slabs in flight");
-      if (NST > 3 && after == 2)
-        wait_vm_barrier<2 * L>();
-      else if (NST > 2 && after == 1)
+      static_assert(NST == 2 || NST == 3, "the waits below cover one slab in flight");
+      if (NST > 2 && after == 1)
         wait_vm_barrier<L>();
       else
         wait_vm_barrier<0>();
