@@ -144,9 +144,12 @@ typedef struct muon_plan_info {
   int32_t n_buckets;                 /* distinct (m, n, padded shape, kernel class) */
   int32_t device;                    /* HIP device the plan lives on, -1 if host-only */
   int64_t workspace_bytes;           /* bytes muon_step needs */
-  int64_t launches_per_step;         /* kernel launches of one muon_step at max_ns_steps, with one
-                                        of edge strips for every B*X of a 256-tile group that has
-                                        them (a B*X that runs on small tiles needs none) */
+  int64_t launches_per_step;         /* most kernel launches of one muon_step at max_ns_steps: every
+                                        group of matrices makes its own, and every B*X of a group
+                                        with edge strips one more for them, as with launch timing
+                                        on.  Without it small groups share launches (5 steps
+                                        of 8 small matrices: 19 issued, 34 counted here), and a
+                                        B*X on small tiles needs no launch for strips. */
   double ns_flops_per_ns_step;       /* algorithmic flops of one NS step of Eq. 2 over all
                                         matrices: sum of 3 m^2 n + m^3 (symmetry-aware) */
   double padded_flops_per_ns_step;   /* flops those steps issue on padded tiles */
@@ -232,9 +235,15 @@ MUON_API muon_status muon_plan_matrix_info(muon_plan plan, int32_t index, muon_m
  * Successive steps on one plan must be ordered on the GPU (one stream, or
  * ordered by the caller): each refresh overwrites the device table the
  * previous step's kernels read.
+ * These streams have the default priority, whatever hip_stream's is, and may
+ * share a hardware queue with other streams of the process: a step can then
+ * wait for work enqueued there before.
  * A call on the same buffers as the previous call (with launch timing off)
- * enqueues kernels only, so it can be captured in a HIP graph and replayed;
- * each replay is bitwise the step an eager call would make.  The scalars
+ * enqueues kernels, and the events that fork and join the plan's streams, only,
+ * so it can be captured in a HIP graph and replayed: the events become
+ * edges of the graph.  The plan's streams belong to the capture while it
+ * lasts, so no other step of this plan may be enqueued until it has ended.
+ * Each replay is bitwise the step an eager call would make.  The scalars
  * (lr, momentum_coef, weight_decay, ns_steps, nesterov) are captured by
  * value: a new value needs a new capture.  A call whose pointers differ
  * from the previous call's returns INVALID_ARG while its stream is being
