@@ -67,6 +67,7 @@ struct MatDev {
   int32_t gram;                // runs the Gram-space recurrence
   int32_t m;                   // oriented unpadded m
   int32_t x_f16;               // 16-bit X and square buffers are fp16 (else bf16)
+  int32_t whole_diag;          // diagonal tiles of square outputs are stored as computed (the 64 classes)
 };
 
 // One output tile of a grouped GEMM launch.

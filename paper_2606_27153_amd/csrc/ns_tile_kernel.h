@@ -52,8 +52,13 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
   // A diagonal tile of a symmetric product keeps the 32 x 32 blocks on or
   // below the diagonal (bmask), stored transposed in their mirror position,
   // and those below it (rmask) also as computed: the rule of the 256 tile, so
-  // that an element's value does not depend on the tile that computed it.
-  const bool dtile = STAGE != ST_BX && ti == tj;
+  // that an element's value does not depend on the tile that computed it.  A
+  // matrix of a 64 class never runs on another tile, and its diagonal tiles are
+  // stored whole, in the one pass that the transposed copy is: with the masked
+  // rule's two passes a step of one 64 x 64 matrix took 68.2 us instead of 65.4.
+  const bool diag = STAGE != ST_BX && ti == tj;
+  const bool whole = TILE == 64 && diag && d.whole_diag != 0;
+  const bool dtile = diag && !whole;
   uint32_t bmask = 0, rmask = 0;
   if (dtile) {
 #pragma unroll
@@ -216,7 +221,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
   const int64_t row0 = int64_t(ti) * TILE + wrow;
   const int64_t col0 = int64_t(tj) * TILE + wn * C::WTN;
   char* region = lds + wid * C::WAVE_LDS;
-  if (STAGE == ST_POLY && dtile && args.diag != 0.f) {
+  if (STAGE == ST_POLY && diag && args.diag != 0.f) {
     // diag * I on the real diagonal (the padding stays zero)
 #pragma unroll
     for (int i = 0; i < C::NBM; ++i)
@@ -243,7 +248,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
     if (rmask) store_rows_via_lds<C, E, true>(acc, region, out_r, ld_r, row0, col0, lane, rmask);
   } else {
     if (!TRB) store_t_via_lds<C, E>(acc, region, out_t, mp, row0, col0, lane);
-    store_rows_via_lds<C, E>(acc, region, out_r, ld_r, row0, col0, lane);
+    if (!whole) store_rows_via_lds<C, E>(acc, region, out_r, ld_r, row0, col0, lane);
   }
 }
 

@@ -669,6 +669,7 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
       d.ew_tiles_c = int32_t(h.cols_pad / EW_TILE);
       d.gram = h.gram;
       d.m = int32_t(h.m);
+      d.whole_diag = kClasses[h.kclass].tile == 64;
     }
     w.ew_tiles = ew;
     w.bytes_momentum = 0;

@@ -91,6 +91,15 @@ int main(int argc, char** argv) {
         }
       }
     }
+  // diagonal tiles are stored whole in the 64 classes, whose launches all run on
+  // the 64 tile (any other class's values must not depend on the launch's tile)
+  for (size_t i = 0; i < p.order.size(); ++i)
+    if ((p.h_matdev[i].whole_diag != 0) != (class_info(p.mats[size_t(p.order[i])].kclass).tile == 64))
+      return fail("rule of the diagonal tiles");
+  for (const WaveHost& w : p.waves)
+    for (const ClassLaunch& cl : w.launches)
+      for (const StageRun* run : {&cl.run_gram, &cl.run_square, &cl.run_full})
+        if (class_info(cl.kclass).tile == 64 && run->exec != EX_64_RING3) return fail("64 class on another tile");
   std::printf("OK %d %d %d %d %d %d %d\n", used[0], used[1], used[2], used[3], modes[0], modes[1],
               modes[2]);
   return 0;
