@@ -442,6 +442,8 @@ void gram_ops(const Plan& p, int32_t ns_steps, OpList& out) {
 }
 
 int64_t launches_per_step(const Plan& p, int32_t ns_steps) {
+  // Every group on launches of its own (as with launch timing on) and every
+  // B*X with edge strips on its class's tiles: an upper count (WaveMode, exec_tile).
   // Per (class, form) group, lower-tile stages and B*X stages.  Eq. 2: Gram,
   // A*A and B*X per step (a cubic step, c = 0, has no A*A).  Gram space, per
   // segment of L steps: the Gram product and B*X once, P_i per step, P Q and
