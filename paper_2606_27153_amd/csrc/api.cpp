@@ -256,8 +256,9 @@ muon_status step_impl(muon_plan plan, void* const* params, const void* const* gr
   // kPtrChunk entries travel in the momentum launches; a longer table goes into
   // the next slot of the plan's pinned ring and is copied on the caller's
   // stream, ahead of the step's kernels.  The host waits only if that slot's
-  // previous copy (kRing refreshes ago) has not run yet.  The workspace's memory is vetted when it changes (two HIP queries); the other
-  // buffers' only on plans created with MUON_PLAN_CHECK_BUFFERS.
+  // previous copy (kRing refreshes ago) has not run yet.  The workspace's
+  // memory is vetted when it changes (two HIP queries); the other buffers'
+  // only on plans created with MUON_PLAN_CHECK_BUFFERS.
   bool changed = !p.ptrs_valid;
   for (size_t i = 0; i < n && !changed; ++i) {
     const PtrEntry& h = p.h_ptrs[i];

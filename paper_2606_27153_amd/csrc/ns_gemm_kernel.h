@@ -18,8 +18,9 @@
 //                                 symmetric: lower tiles + mirror
 //   ST_BX    s (a X + B X)        all tiles; a X folded in from the resident
 //                                 slab of X; X' in the next ping-pong buffer,
-//                                 or, on the last step, O in fp32 in the
-//                                 matrix's own (un-oriented) layout
+//                                 or, on the last step, the update of W (and
+//                                 O, if asked for) in the matrix's own
+//                                 (un-oriented) layout
 //
 // Eq. 2 runs GRAM, POLY, BX per NS step; the Gram-space recurrence runs, per
 // segment of at most gram_restart steps, GRAM once, then POLY (P_i = a I +
