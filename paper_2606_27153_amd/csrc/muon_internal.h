@@ -67,20 +67,23 @@ struct MatDev {
   int32_t gram;                // runs the Gram-space recurrence
   int32_t m;                   // oriented unpadded m
   int32_t x_f16;               // 16-bit X and square buffers are fp16 (else bf16)
-  int32_t whole_diag;          // diagonal tiles of square outputs are stored as computed (the 64 classes)
 };
 
 // One output tile of a grouped GEMM launch.
 struct TileEntry {
   int32_t mat;     // index into the MatDev array (global, wave order)
   int32_t ti, tj;  // output tile row and column
-  int32_t flags;   // kTileHalf: only the first half of the tile's rows
+  int32_t flags;   // kTileHalf, kTileWhole
 };
 // A 256 tile of a square (m x m) output of which only the top 128 rows
 // exist: the row strip of a matrix whose m ends 128 or fewer past a multiple
 // of 256.  Its operand panels hold 128 real rows (the padded extent ends
 // there) and its 8 waves share those rows, 64 each (see ns_gemm_kernel.h).
 constexpr int32_t kTileHalf = 1;
+// A tile of a square output that lies in a diagonal tile of its matrix's class,
+// where the class stores those whole (whole_diagonals in plan.cpp): it is stored
+// transposed only, and the list holds its mirror tile as well.
+constexpr int32_t kTileWhole = 2;
 
 // Per-matrix device pointers, refreshed when the caller's buffers change.
 struct PtrEntry {

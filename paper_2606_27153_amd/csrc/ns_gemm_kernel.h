@@ -932,7 +932,9 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
   // the K loop, with the blocks masked; each computed block is stored
   // transposed in its mirror position, and a block below the diagonal also as
   // computed, so the stored tile is symmetric like every off-diagonal pair.
-  const bool dtile = STAGE != ST_BX && ti == tj;
+  // (A matrix one tile wide is left whole, stored in one pass: kTileWhole.)
+  const bool whole = STAGE != ST_BX && (te.flags & kTileWhole) != 0;
+  const bool dtile = STAGE != ST_BX && ti == tj && !whole;
   // A half tile (kTileHalf: the row strip of a matrix whose padded m ends 128
   // rows into this tile) has only its top 128 rows, and its own operand
   // panel (on the diagonal of a square output, the other one too) only 128
@@ -1189,6 +1191,8 @@ __global__ __launch_bounds__(512) void ns_gemm_kernel(GemmArgs args) {
   } else if (masked) {  // square outputs only
     if (dlive)
       store_piece16<C, E, true, true, true>(acc, region, out_t, mp, out_r, ld_r, row0, col0, lane, bmask, rmask);
+  } else if (whole) {
+    store_piece16<C, E, true, false, false>(acc, region, out_t, mp, out_r, ld_r, row0, col0, lane);
   } else {
     store_piece16<C, E, STAGE != ST_BX, true, false>(acc, region, out_t, mp, out_r, ld_r, row0, col0, lane);
   }

@@ -49,15 +49,15 @@ __device__ __forceinline__ void run_tile(const GemmArgs& args, int block, char* 
   const int ti = te.ti, tj = te.tj;
   const int wm = wid / 2, wn = wid % 2;
   const int wrow = wm * C::WTM;
-  // A diagonal tile of a symmetric product keeps the 32 x 32 blocks on or
-  // below the diagonal (bmask), stored transposed in their mirror position,
-  // and those below it (rmask) also as computed: the rule of the 256 tile, so
-  // that an element's value does not depend on the tile that computed it.  A
-  // matrix of a 64 class never runs on another tile, and its diagonal tiles are
-  // stored whole, in the one pass that the transposed copy is: with the masked
-  // rule's two passes a step of one 64 x 64 matrix took 68.2 us instead of 65.4.
+  // The two halves of a symmetric product round differently, so which of them
+  // is stored follows the matrix's class, not the tile that this launch runs
+  // on.  Where the class stores diagonal tiles whole, the tiles inside one
+  // (kTileWhole) are stored as computed, in the one pass that the transposed
+  // copy is.  Elsewhere (256 classes of several tiles) a diagonal tile keeps
+  // the 32 x 32 blocks on or below the diagonal (bmask), stored transposed in
+  // their mirror position, and those below it (rmask) also as computed.
   const bool diag = STAGE != ST_BX && ti == tj;
-  const bool whole = TILE == 64 && diag && d.whole_diag != 0;
+  const bool whole = STAGE != ST_BX && (te.flags & kTileWhole) != 0;
   const bool dtile = diag && !whole;
   uint32_t bmask = 0, rmask = 0;
   if (dtile) {

@@ -91,6 +91,18 @@ int32_t choose_class(int64_t m, int64_t n, const muon_plan_opts& o, int32_t tile
   return best;
 }
 
+// Whether the diagonal tiles of a matrix's square outputs are stored whole, as
+// computed, or as their lower triangle and its mirror (matrices of several 256
+// tiles, where that spares 28 of a diagonal tile's 64 MFMA blocks).  In a matrix
+// one tile wide and in the small classes the second store pass costs more than
+// the skipped blocks save: a step of one 64 x 64 matrix took 68.2 us with it,
+// 65.4 without.  The class decides, so that a value does not depend on the
+// tile that a launch runs on.
+bool whole_diagonals(const MatHost& h) {
+  const int32_t tile = kClasses[h.kclass].tile;
+  return tile < 256 || h.m_pad == tile;
+}
+
 // Full tiles (all tm x tn output tiles) of one matrix, cut into units of up
 // to 4 row panels x 8 column panels: the 32 tiles of a unit, about the
 // number of blocks one XCD runs at once, read 4 + 8 operand panels, so an
@@ -117,8 +129,9 @@ void full_units(std::vector<std::vector<TileEntry>>& units, int32_t mat, int64_t
 // off-diagonal 8 x 8 block is two 4 x 8 units.  A unit reads at most 8 row
 // panels of each operand (a diagonal unit of a product with itself, 8 in
 // all), so the blocks of one XCD working through a unit share panels in
-// that XCD's L2.
-void lower_units(std::vector<std::vector<TileEntry>>& units, int32_t mat, int64_t tm) {
+// that XCD's L2.  whole > 0: the whole x whole tiles of each diagonal tile of
+// the matrix's class are all listed, and stored as computed (whole divides 8).
+void lower_units(std::vector<std::vector<TileEntry>>& units, int32_t mat, int64_t tm, int64_t whole) {
   for (int64_t r0 = 0; r0 < tm; r0 += 8) {
     const int64_t r1 = std::min(tm, r0 + 8);
     for (int64_t c0 = 0; c0 < r0; c0 += 8)
@@ -128,8 +141,11 @@ void lower_units(std::vector<std::vector<TileEntry>>& units, int32_t mat, int64_
           for (int64_t tj = c0; tj < c0 + 8; ++tj) units.back().push_back(TileEntry{mat, int32_t(ti), int32_t(tj), 0});
       }
     units.emplace_back();
-    for (int64_t ti = r0; ti < r1; ++ti)
-      for (int64_t tj = r0; tj <= ti; ++tj) units.back().push_back(TileEntry{mat, int32_t(ti), int32_t(tj), 0});
+    for (int64_t ti = r0; ti < r1; ++ti) {
+      const int64_t w0 = whole ? ti / whole * whole : ti + 1;  // first column of the whole part
+      for (int64_t tj = r0; tj < (whole ? w0 + whole : w0); ++tj)
+        units.back().push_back(TileEntry{mat, int32_t(ti), int32_t(tj), tj >= w0 ? kTileWhole : 0});
+    }
   }
 }
 
@@ -202,11 +218,14 @@ struct TileLoad {
   int64_t m_pad, n_pad;   // n_pad = 0: a symmetric output (lower tiles)
   int64_t slabs;
   bool fp32;
+  int64_t whole;          // symmetric output: the class's tile if its diagonal tiles are stored whole, else 0
 };
 
 int64_t tile_count(const TileLoad& t, int64_t tile) {
   const int64_t a = t.m_pad / tile, b = t.n_pad / tile;
-  return t.n_pad ? a * b : a * (a + 1) / 2;
+  if (t.n_pad) return a * b;
+  const int64_t w = t.whole ? t.whole / tile : 1;
+  return (a * (a + 1) + a * (w - 1)) / 2;
 }
 
 // Time of one slab of a tile when `tiles` of them share the chip.
@@ -671,7 +690,6 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
       d.ew_tiles_c = int32_t(h.cols_pad / EW_TILE);
       d.gram = h.gram;
       d.m = int32_t(h.m);
-      d.whole_diag = kClasses[h.kclass].tile == 64;
     }
     w.ew_tiles = ew;
     w.bytes_momentum = 0;
@@ -708,7 +726,7 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
           if (is_full)
             full_units(u, wv.first + s, h.m_pad / t, h.n_pad / t);
           else
-            lower_units(u, wv.first + s, h.m_pad / t);
+            lower_units(u, wv.first + s, h.m_pad / t, whole_diagonals(h) ? kClasses[h.kclass].tile / t : 0);
         }
         interleave_units(out, u);
         list.off = int64_t(p.h_tiles.size());
@@ -743,7 +761,7 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
         fp += m * m * m;
         fb += 2 * m * m * nn;
         const int64_t tm = h.m_main / tile, tn = h.n_main / tile;
-        lower_units(units, pos, tm);
+        lower_units(units, pos, tm, whole_diagonals(h) ? 1 : 0);
         full_units(funits, pos, tm, tn);
         // edge strips: the lower row strip of the square outputs on half
         // tiles of this class, one unit per matrix (its last tile on the
@@ -798,9 +816,10 @@ muon_status build_plan(const muon_matrix_desc* descs, int32_t n, const muon_plan
         const bool f32 = kClasses[kc].fp32 != 0;
         const int64_t bk = f32 ? 32 : 64;
         const int64_t sm = (h.m + bk - 1) / bk, sn = (h.n + bk - 1) / bk;
-        gl.gram.push_back(TileLoad{h.m_pad, 0, sn, f32});
-        gl.square.push_back(TileLoad{h.m_pad, 0, sm, f32});
-        gl.full.push_back(TileLoad{h.m_pad, h.n_pad, sm, f32});
+        const int64_t whole = whole_diagonals(h) ? tile : 0;
+        gl.gram.push_back(TileLoad{h.m_pad, 0, sn, f32, whole});
+        gl.square.push_back(TileLoad{h.m_pad, 0, sm, f32, whole});
+        gl.full.push_back(TileLoad{h.m_pad, h.n_pad, sm, f32, 0});
       }
       auto stage_run = [&](const std::vector<TileLoad>& loads, bool is_full, double* us) {
         const int64_t own = is_full ? cl.n_full + cl.n_strip_full : cl.n_lower;

@@ -1,9 +1,10 @@
 // Host-only check of the tile lists that launches really run on (built with
 // g++ from csrc/plan.cpp by tests/test_exec_tiles.py).  A launch with too few
 // tiles of its class to fill the chip runs on smaller tiles: for every group
-// and kind of launch, the run's list must cover the group's padded outputs
-// exactly once (lower tiles: every cell on or below the diagonal, directly or
-// inside a diagonal tile) with a tile that divides the padding, and large
+// and kind of launch, the run's list must store every cell of the group's padded
+// outputs exactly once with a tile that divides the padding (lower tiles: a
+// tile on the diagonal, a pair of mirror tiles, or, inside a diagonal tile of a
+// class that stores those whole, every tile in its mirror place), and large
 // groups must keep their class tiles.  Arguments: precision.  Prints "OK", how
 // many runs use each kernel, and how many waves have each mode.
 #include <cstdio>
@@ -70,7 +71,7 @@ int main(int argc, char** argv) {
           const MatHost& h = p.mats[size_t(p.order[size_t(w.first + s)])];
           if (h.kclass != cl.kclass || h.gram != cl.gram) continue;
           if (h.m_pad % t || h.n_pad % t) return fail("tile does not divide the padding");
-          cells[w.first + s].assign(size_t(h.m_pad / t) * size_t((full ? h.n_pad : h.m_pad) / t), 0);
+          cells[w.first + s].assign(size_t(h.m_pad / t) * size_t((full ? h.n_pad : h.m_pad) / t), 0);  // stores
         }
         for (int32_t i = 0; i < run.n; ++i) {
           const TileEntry& e = p.h_tiles[size_t(run.off + i)];
@@ -78,28 +79,22 @@ int main(int argc, char** argv) {
           if (it == cells.end()) return fail("tile of another group");
           const MatHost& h = p.mats[size_t(p.order[size_t(e.mat)])];
           const long long cm = h.m_pad / t, cn = (full ? h.n_pad : h.m_pad) / t;
-          if (e.flags || e.ti < 0 || e.tj < 0 || e.ti >= cm || e.tj >= cn) return fail("tile out of range");
-          if (!full && e.tj > e.ti) return fail("tile above the diagonal");
-          if (++it->second[size_t(e.ti * cn + e.tj)] != 1) return fail("duplicate tile");
+          if (e.ti < 0 || e.tj < 0 || e.ti >= cm || e.tj >= cn) return fail("tile out of range");
+          // which half of a product is stored follows the class: its diagonal
+          // tiles whole, but for matrices of several 256 tiles
+          const int per = ci.tile / t;
+          const bool whole = !full && e.ti / per == e.tj / per && (ci.tile < 256 || h.m_pad == 256);
+          if (e.flags != (whole ? kTileWhole : 0)) return fail("rule of the diagonal tiles");
+          if (!full && !whole && e.tj > e.ti) return fail("tile above the diagonal");
+          if (full || !whole) ++it->second[size_t(e.ti * cn + e.tj)];
+          if (!full && (whole || e.ti != e.tj)) ++it->second[size_t(e.tj * cn + e.ti)];
         }
         for (const auto& kv : cells) {
-          const MatHost& h = p.mats[size_t(p.order[size_t(kv.first)])];
-          const long long cm = h.m_pad / t, cn = (full ? h.n_pad : h.m_pad) / t;
-          for (long long i = 0; i < cm; ++i)
-            for (long long j = 0; j < (full ? cn : i + 1); ++j)
-              if (kv.second[size_t(i * cn + j)] != 1) return fail("outputs not covered");
+          for (int v : kv.second)
+            if (v != 1) return fail("outputs not stored exactly once");
         }
       }
     }
-  // diagonal tiles are stored whole in the 64 classes, whose launches all run on
-  // the 64 tile (any other class's values must not depend on the launch's tile)
-  for (size_t i = 0; i < p.order.size(); ++i)
-    if ((p.h_matdev[i].whole_diag != 0) != (class_info(p.mats[size_t(p.order[i])].kclass).tile == 64))
-      return fail("rule of the diagonal tiles");
-  for (const WaveHost& w : p.waves)
-    for (const ClassLaunch& cl : w.launches)
-      for (const StageRun* run : {&cl.run_gram, &cl.run_square, &cl.run_full})
-        if (class_info(cl.kclass).tile == 64 && run->exec != EX_64_RING3) return fail("64 class on another tile");
   std::printf("OK %d %d %d %d %d %d %d\n", used[0], used[1], used[2], used[3], modes[0], modes[1],
               modes[2]);
   return 0;

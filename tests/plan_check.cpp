@@ -123,9 +123,17 @@ int main(int argc, char** argv) {
       auto add = [&](std::vector<Rect>& v, int64_t off, int32_t cnt, int t) {
         for (int32_t i = 0; i < cnt; ++i) {
           const TileEntry& e = p.h_tiles[size_t(off + i)];
-          if (e.flags & ~kTileHalf || ((e.flags & kTileHalf) && t != 256)) bad_flags = true;
           // the kernels index the wave's flags and scales by mat - first
-          if (e.mat < w.first || e.mat >= w.first + w.count) bad_mat = true;
+          if (e.mat < w.first || e.mat >= w.first + w.count) {
+            bad_mat = true;
+            continue;
+          }
+          // diagonal tiles are stored whole but for matrices of several 256 tiles
+          const MatHost& h = p.mats[size_t(p.order[size_t(e.mat)])];
+          const bool whole = &v == &lower && e.ti == e.tj && (t < 256 || h.m_pad == 256);
+          if ((e.flags & ~kTileWhole) != ((e.flags & kTileHalf) && t == 256 ? kTileHalf : 0) ||
+              ((e.flags & kTileWhole) != 0) != whole)
+            bad_flags = true;
           const long long k = t / 64;
           v.push_back(Rect{e.mat, (long long)e.ti * k, (long long)e.tj * k, (e.flags & kTileHalf) ? k / 2 : k, k});
         }
