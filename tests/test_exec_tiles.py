@@ -59,8 +59,11 @@ def test_lists_cover_outputs(lists_check, precision):
 
 # one matrix shape, and how many of it leave the small tiles: one-tile and
 # two-tile squares, half tiles and edge strips on both sides, a tall and a wide
-# Gram-space matrix, odd columns, the 128 and 64 classes
-SHAPES = [((256, 256), 300), ((512, 512), 150), ((640, 640), 120), ((384, 1100), 150), ((1152, 385), 150),
+# Gram-space matrix, odd columns, the 128 and 64 classes; one-tile matrices whose
+# square products of either form run on the 256 tile, with a wave block of
+# padding and without
+SHAPES = [((180, 700), 600), ((256, 400), 1100), ((256, 256), 300), ((512, 512), 150), ((640, 640), 120),
+          ((384, 1100), 150), ((1152, 385), 150),
           ((300, 301), 200), ((130, 700), 300), ((96, 520), 400), ((40, 200), 900)]
 
 
