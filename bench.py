@@ -52,6 +52,14 @@ def kernel_sources_hash() -> str:
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "traffic_summary.txt")
 
 
+def traffic_applies(args) -> bool:
+    """Whether the run launches what the committed traffic summary was taken
+    on: the whole 8B set with the plan's defaults."""
+    from paper_2606_27153_amd.optim import default_gram_min_aspect
+    return (args.config == "8b" and args.owner_share == 1 and args.wave_bytes == 0 and not args.autotune
+            and args.gram_min_aspect == default_gram_min_aspect(args.precision))
+
+
 def read_traffic(kernel_key: str, path: str = TRAFFIC_SUMMARY):
     """HBM bytes per launch of ``kernel_key`` from the committed rocprofv3
     --pmc summary, if it was taken on the current kernel sources."""
@@ -692,7 +700,7 @@ def main(argv=None) -> int:
                     "frac": round(achieved / PEAK_HBM_GBS, 4)}
         roof["kernel"] = dom_key
         roof["mean_launch_ms"] = round(dom["total_ms"] / dom["launches"], 4)
-        traffic = read_traffic(dom_key)
+        traffic = read_traffic(dom_key) if traffic_applies(args) else None
         roof["traffic"] = None if traffic is None else round(traffic)
         if dom["kind"] in GEMM_KINDS:
             launches_per_step = dom["launches"] / split

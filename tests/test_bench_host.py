@@ -4,6 +4,7 @@ LPT split of the owner-share diagnostic, on host-only plans."""
 import os
 import subprocess
 import sys
+import types
 
 import numpy as np
 import pytest
@@ -71,6 +72,14 @@ def test_traffic_summary_round_trip(tmp_path):
     got = bench.read_traffic("symm:bf16_t256", path=str(out))
     assert got == pytest.approx((200.0 * 2 + 50.0 * 1) * 1024)
     assert bench.read_traffic("bx:bf16_t256", path=str(out)) is None
+
+
+def test_traffic_is_reported_for_the_set_it_was_taken_on():
+    run = dict(config="8b", precision="bf16", owner_share=1, wave_bytes=0, autotune=False, gram_min_aspect=1.4)
+    assert bench.traffic_applies(types.SimpleNamespace(**run))
+    for other in (dict(config="tiny"), dict(config="moe"), dict(owner_share=8), dict(wave_bytes=1 << 30),
+                  dict(autotune=True), dict(gram_min_aspect=0.0)):
+        assert not bench.traffic_applies(types.SimpleNamespace(**{**run, **other}))
 
 
 def test_ns_cost_matches_the_plan_accounting():
